@@ -56,7 +56,11 @@ static const int kTileM[TILE_VARIANTS] = {256, 256, 128};
 static const int kTileN[TILE_VARIANTS] = {256, 224, 128};
 typedef TileCfg<256, 256, 2, 4, 32, 4> Cfg256x256;
 typedef TileCfg<256, 224, 8, 1, 32, 4> Cfg256x224;
-typedef TileCfg<128, 128, 2, 2, 32, 4> Cfg128x128;
+// The 128x128 tile steps 64 along K: a row of its A stage is then a whole 128-byte line (half a line with 32) and the ring
+// holds twice the bytes in flight, which is what bounds a tile with one wave per SIMD.  Measured, [512,8192] x [8192,3584]
+// (112 tiles): 65 -> 52 us, 466 -> 371 cycles per 32 of K; 2048^2 x 8192 (256 tiles): 71.6 -> 65.9 us.  More stages of 32
+// do not help (6 or 8 instead of 4: 66 us).
+typedef TileCfg<128, 128, 2, 2, 64, 4> Cfg128x128;
 // Row tiles of a grouped GEMM with at most 64 rows (the rest of an expert's rows): their time is the streaming of the
 // expert's weight block, which is bound by the bytes in flight -- seven stages of 4 + 16 KiB instead of four of 16 + 16.
 typedef TileCfg<64, 256, 2, 4, 32, 7> Cfg64x256;
