@@ -186,8 +186,14 @@ int tl_read_clocks(tl_ctx* ctx, void* workspace /*dev*/, long long* out /*host, 
  *              tiles per call, so the caller zeroes the workspace together with the flags (once, or when `epoch`
  *              restarts at 1).  Bytes 16..23 hold the start time of the call in flight when link_gbps is set.  One call at
  *              a time per workspace.  In WAVES and SIDE_KERNEL mode producer tiles are handed out through this queue to the
- *              producer workgroups and to GEMM workgroups that would otherwise wait.
- *   compute_stream receives the fused kernel; comm_stream the copies in TL_COMM_STREAM.
+ *              producer workgroups and to GEMM workgroups that would otherwise wait -- or, where the launch is one round of
+ *              workgroups, split over all of them by index.  Where several workgroups share a tile along K the query asks
+ *              for more than 256 bytes (counters and fp32 partial tiles behind the first 256); with 256 bytes the same call
+ *              computes whole tiles (the sums then differ in their last bits).
+ *   compute_stream receives the fused kernel; comm_stream the copies in TL_COMM_STREAM and COPY_ENGINE mode.  In SIDE_KERNEL
+ *   mode the producers join the GEMM's launch (GEMM workgroups copy there in any case, so nothing of the gather can be relied
+ *   on in comm_stream's order alone); a kernel of their own on comm_stream they are with comm_workgroups, link_gbps or
+ *   comm_alone set.
  */
 int tl_ag_gemm(tl_ctx* ctx, const void* const* a_shards /*host array of dev*/, void* a_gathered, const void* b,
                void* c, int M, int N, int K, unsigned* flags /*dev*/, unsigned epoch, void* workspace /*dev*/,

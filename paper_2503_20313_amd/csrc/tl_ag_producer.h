@@ -79,10 +79,9 @@ __device__ __forceinline__ bool claim_ticket(const AgProducer& p, unsigned* out)
   return true;
 }
 
-// All threads of the workgroup call this with the same ticket index; `wave` is the wave-uniform wave index.
-// DEPTH = loads in flight per lane of the copy.
-template <int DEPTH>
-__device__ __forceinline__ void produce_tile(const AgProducer& p, int i, int tid, int wave, int nthreads) {
+// Where ticket i lies: row tile tm (of the whole gathered matrix), column tile tn, source rank, channel.
+struct ProducerPlace { int tm, tn, src, channel; };
+__device__ __forceinline__ ProducerPlace producer_place(const AgProducer& p, int i) {
   const int ptm_per_rank = p.rows_per_rank / p.Tm_p;
   int tmi, tn;
   if (p.k_chunks > 1) { tn = i / p.n_ptm; tmi = i - tn * p.n_ptm; }
@@ -98,25 +97,108 @@ __device__ __forceinline__ void produce_tile(const AgProducer& p, int i, int tid
     tm = tmi + p.first_src * ptm_per_rank;  // ring order over source ranks: first_src, first_src+1, ...
     if (tm >= p.n_ptm_all) tm -= p.n_ptm_all;
   }
-  int row_lo = tm * p.Tm_p;
-  int src = tm / ptm_per_rank;                       // f_R
-  int channel = tm / (p.rows_per_channel / p.Tm_p);  // f_C
-  if (p.pace_q8 && src != p.rank) {
+  return {tm, tn, tm / ptm_per_rank /* f_R */, tm / (p.rows_per_channel / p.Tm_p) /* f_C */};
+}
+
+__device__ __forceinline__ unsigned* producer_flag(const AgProducer& p, const ProducerPlace& t) {
+  return p.flags + (p.k_chunks > 1 ? t.channel * p.k_chunks + t.tn : t.channel);
+}
+
+// Starts the copy of a producer tile (nothing to do for the local shard in place); the stores may still be on their way.
+template <int DEPTH>
+__device__ __forceinline__ void copy_producer_tile(const AgProducer& p, const ProducerPlace& t, int tid, int nthreads) {
+  if (t.src == p.rank && p.local_in_place) return;
+  const int row_lo = t.tm * p.Tm_p;
+  const bf16_t* s = p.shards[t.src] + (long)(row_lo - t.src * p.rows_per_rank) * p.ld + (long)t.tn * p.Tn_p;
+  bf16_t* d = p.gathered + (long)row_lo * p.ld + (long)t.tn * p.Tn_p;
+  copy_tile<DEPTH>(s, p.ld, d, p.ld, p.Tm_p, p.Tn_p, tid, nthreads);
+}
+
+// All threads of the workgroup call this with the same ticket index; `wave` is the wave-uniform wave index.
+// DEPTH = loads in flight per lane of the copy.
+template <int DEPTH>
+__device__ __forceinline__ void produce_tile(const AgProducer& p, int i, int tid, int wave, int nthreads) {
+  const ProducerPlace t = producer_place(p, i);
+  if (p.pace_q8 && t.src != p.rank) {
     // the links of all source ranks run side by side; this tile is number `nth` of what its rank sends
-    const int jm = tm - src * ptm_per_rank;
-    const int nth = p.k_chunks > 1 ? tn * ptm_per_rank + jm : jm * p.n_ptn + tn;
+    const int ptm_per_rank = p.rows_per_rank / p.Tm_p, jm = t.tm - t.src * ptm_per_rank;
+    const int nth = p.k_chunks > 1 ? t.tn * ptm_per_rank + jm : jm * p.n_ptn + t.tn;
     const unsigned long long due = ((unsigned long long)(nth + 1) * p.pace_q8) >> 8;
     const unsigned long long t0 = pace_start(p);
     while ((((unsigned long long)wall_clock64() - t0) & ((1ull << 40) - 1)) < due) __builtin_amdgcn_s_sleep(8);
   }
-  if (!(src == p.rank && p.local_in_place)) {
-    const bf16_t* s = p.shards[src] + (long)(row_lo - src * p.rows_per_rank) * p.ld + (long)tn * p.Tn_p;
-    bf16_t* d = p.gathered + (long)row_lo * p.ld + (long)tn * p.Tn_p;
-    copy_tile<DEPTH>(s, p.ld, d, p.ld, p.Tm_p, p.Tn_p, tid, nthreads);
-  }
+  copy_producer_tile<DEPTH>(p, t, tid, nthreads);
   wait_all_vmem();  // this wave's written-through stores are complete ...
   __syncthreads();  // ... and so are every other wave's: the tile is where every die sees it
-  if (wave == 0) lane0_add(p.flags + (p.k_chunks > 1 ? channel * p.k_chunks + tn : channel), 1u);
+  if (wave == 0) lane0_add(producer_flag(p, t), 1u);
+}
+
+// ======================================================================================
+// The gather as shares, for launches that are one round of workgroups (a queue hands out tiles at 11 ns each -- adds to one
+// address follow one another -- and costs every workgroup several trips to memory per tile: 20 us before the first tile of
+// [512,8192] x [8192,3584] could start, 8 us as shares): workgroup `part` of `parts` copies tickets [lo, hi) x part / parts,
+// all copies in flight together, and notifies once per channel.  A workgroup that is not on the chip keeps its share back;
+// consumer_wait_shared helps itself after a while, so nobody depends on it for good.
+// ======================================================================================
+template <int DEPTH>
+__device__ __forceinline__ void gather_share(const AgProducer& p, int lo, int hi, int part, int parts, int tid, int nthreads) {
+  const int first = lo + (int)((long)(hi - lo) * part / parts), end = lo + (int)((long)(hi - lo) * (part + 1) / parts);
+  if (first >= end) return;
+  for (int i = first; i < end; i++) copy_producer_tile<DEPTH>(p, producer_place(p, i), tid, nthreads);
+  wait_all_vmem();
+  __syncthreads();   // every wave's written-through stores are complete
+  if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
+    unsigned* flag = producer_flag(p, producer_place(p, first));
+    unsigned n = 1;
+    for (int i = first + 1; i < end; i++) {
+      unsigned* f = producer_flag(p, producer_place(p, i));
+      if (f != flag) { lane0_add(flag, n); flag = f; n = 0; }
+      n++;
+    }
+    lane0_add(flag, n);
+  }
+}
+
+// consumer_tile_wait on a gather by shares: all channels' flags in one look (lane c polls channel c).  After kShareGrace
+// ticks without them the workgroup copies the missing rows itself -- the same bytes, so it does not matter that their owner
+// copies and notifies them as well once it runs -- and goes on.
+constexpr unsigned long long kShareGrace = 20000;   // 200 us on the 100 MHz clock
+template <int DEPTH>
+__device__ __forceinline__ void consumer_wait_shared(const AgProducer& p, unsigned long long chan_mask, int tid, int nthreads, int* s_state) {
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int first = __builtin_ctzll(chan_mask);
+  unsigned long long missing = 0;
+  if (wave == 0) {
+    const unsigned long long t0 = wall_clock64();
+    const bool mine = (chan_mask >> lane) & 1ull;
+    int give_up = 0;
+    for (;;) {
+      const unsigned f = __hip_atomic_load(p.flags + (mine ? lane : first) * p.k_chunks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      missing = __builtin_amdgcn_ballot_w64(mine && (int)(f - p.wait_target) < 0);
+      if (!missing) break;
+      const unsigned long long waited = wall_clock64() - t0;
+      if (waited > kShareGrace) { give_up = 1; break; }
+      __builtin_amdgcn_s_sleep(2);
+    }
+    *s_state = give_up;
+    s_state[1] = (int)(unsigned)missing;
+    s_state[2] = (int)(unsigned)(missing >> 32);
+  }
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(*s_state)) {
+    missing = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(s_state[1]) | ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(s_state[2]) << 32);
+    const int rows = p.rows_per_channel, cols = p.k_chunks > 1 ? p.Tn_p : p.ld;
+    for (; missing; missing &= missing - 1) {
+      const int row_lo = __builtin_ctzll(missing) * rows, src = row_lo / p.rows_per_rank;
+      if (!(src == p.rank && p.local_in_place))
+        for (int r = 0; r < rows; r += p.Tm_p)   // (a piece of a tile mover spans less than 2 GiB)
+          copy_tile<DEPTH>(p.shards[src] + (long)(row_lo + r - src * p.rows_per_rank) * p.ld, p.ld, p.gathered + (long)(row_lo + r) * p.ld, p.ld, p.Tm_p, cols, tid,
+                           nthreads);
+    }
+    wait_all_vmem();
+  }
+  acquire_after_wait(p.ctl);
+  __syncthreads();
 }
 
 // Push mode (paper: "Data Primitives", push mode): ticket j of the push range is producer tile j % (tiles per shard) of the local shard,
@@ -166,9 +248,11 @@ __device__ __forceinline__ void ag_producer(const AgProducer& p, int tid, int nt
 // the workgroup works off producer tickets; with the queue empty it sleeps and polls (bounded by ctl.timeout).
 // DEPTH = loads in flight per lane when this workgroup copies a producer tile itself: deep where the caller's registers allow
 // (a ticket then takes a quarter of the time), shallow where they are full.
-template <int DEPTH = 2>
+// ONE: the mask has a single channel (a kernel whose registers are full saves the lane arithmetic).
+template <int DEPTH = 2, bool ONE = false>
 __device__ __forceinline__ void consumer_wait_or_produce(const AgProducer& p, unsigned long long chan_mask, int tid, int nthreads, int* s_ticket) {
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int first = __builtin_ctzll(chan_mask);
   unsigned long long t0 = 0;
   if (wave == 0 && (p.ctl.timeout || p.pace_q8)) t0 = wall_clock64();
   // Tickets are taken only while the queue head has not passed the last tile of the awaited channels: beyond that point every
@@ -202,16 +286,15 @@ __device__ __forceinline__ void consumer_wait_or_produce(const AgProducer& p, un
   const unsigned queue_begin = p.ticket_end - (unsigned)(p.n_ptm * p.n_ptn + p.n_out);
   for (;;) {
     if (wave == 0) {
-      int state = -2;  // -2: ready, -1: not ready and nothing to produce, >= 0: ticket to work off
-      int first_short = 0;
-      for (unsigned long long m = chan_mask; m; m &= m - 1) {
-        int ch = __builtin_ctzll(m);
-        unsigned f = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.flags + ch * p.k_chunks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if ((int)(f - p.wait_target) < 0 && state == -2) { state = -1; first_short = ch; }
-      }
+      // one round trip for all channels and the queue head: lane c looks at channel c (lanes of other channels at the first awaited one)
+      const bool mine = ONE || ((chan_mask >> lane) & 1ull);
+      const unsigned f = __hip_atomic_load(p.flags + (mine && !ONE ? lane : first) * p.k_chunks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned head = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      const unsigned long long missing = __builtin_amdgcn_ballot_w64(mine && (int)(f - p.wait_target) < 0);
+      int state = missing ? -1 : -2;  // -2: ready, -1: not ready and nothing to produce, >= 0: ticket to work off
+      const int first_short = ONE ? first : (missing ? __builtin_ctzll(missing) : 0);
       if (state == -1) {
         unsigned t;
-        unsigned head = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         if ((int)(head - queue_begin) < limit && (!patience || wall_clock64() - t0 > patience) && claim_ticket(p, &t)) state = (int)t;
         else if (p.ctl.timeout) {
           int st = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.ctl.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));

@@ -157,8 +157,8 @@ __global__ void __launch_bounds__(512 / QT) sp_attention_kernel(const AttnParams
       return;
     }
     unsigned long long m = 1ull << (row / p.rows_per_channel);
-    consumer_wait_or_produce(p.kprod, m, tid, NT, &s_ticket);
-    consumer_wait_or_produce(p.vprod, m, tid, NT, &s_ticket);
+    consumer_wait_or_produce<2, true>(p.kprod, m, tid, NT, &s_ticket);
+    consumer_wait_or_produce<2, true>(p.vprod, m, tid, NT, &s_ticket);
   };
 
   // ---- per-lane LDS read offsets

@@ -22,6 +22,11 @@ struct AgGemmParams {
   int n_comm;           // producer workgroups at the front of the grid (0: none in this launch)
   int do_compute;       // 0: producers only
   int do_wait;          // 0: no wait, 1: wait on channel flags and help the producers, 2: wait only
+  int share;            // the gather is split over all workgroups of the launch by index instead of handed out by the queue
+  int splits;           // > 1: this many workgroups share every tile, each with split_steps of its K steps (one position per workgroup)
+  int split_steps;
+  float* slots;         // [n_tiles][splits] slots of BM x BN floats
+  unsigned* counts;     // [n_tiles] workgroups that have left their part; each grows by `splits` per call
 };
 
 struct GemmRsParams {
@@ -52,23 +57,37 @@ struct ChunkWait {
   __device__ __forceinline__ void acquire() const { acquire_after_wait(ctl); }
 };
 
-template <class Cfg, bool GATED = false>
+template <class Cfg, bool GATED = false, bool SPLIT = false>
 __global__ void __launch_bounds__(Cfg::NTHREADS) ag_gemm_kernel(const AgGemmParams p) {
   typedef typename std::conditional<GATED, GatedRows, DenseRows>::type Out;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  __shared__ int s_ticket;
+  __shared__ int s_ticket, s_share[3];
   const int tid = threadIdx.x;
   if ((int)blockIdx.x < p.n_comm) {
-    ag_producer(p.prod, tid, Cfg::NTHREADS, &s_ticket);
+    if (p.share) {
+      // with K chunks the first one is everybody's, the others are copied beside the matrix work
+      const int all = p.prod.n_ptm * p.prod.n_ptn, n0 = p.prod.k_chunks > 1 ? p.prod.n_ptm : all;
+      gather_share<8>(p.prod, 0, n0, blockIdx.x, gridDim.x, tid, Cfg::NTHREADS);
+      for (int lo = n0; lo < all; lo += p.prod.n_ptm) gather_share<8>(p.prod, lo, lo + p.prod.n_ptm, blockIdx.x, p.n_comm, tid, Cfg::NTHREADS);
+    } else {
+      ag_producer(p.prod, tid, Cfg::NTHREADS, &s_ticket);
+    }
     return;
   }
   if (!p.do_compute) return;
   __builtin_amdgcn_s_setprio(TL_COMPUTE_WAVE_PRIO);  // matrix waves go first when they share a SIMD with communication waves
   const int w = blockIdx.x - p.n_comm;
   const int M_per_channel = p.prod.rows_per_channel;
+  if (p.share) gather_share<8>(p.prod, 0, p.prod.k_chunks > 1 ? p.prod.n_ptm : p.prod.n_ptm * p.prod.n_ptn, blockIdx.x, gridDim.x, tid, Cfg::NTHREADS);
   const ClockSample cs0 = clock_sample_begin(w);
   for (int pos = w; pos < p.sched.n_tiles; pos += p.sched.G) {
-    int tile = sched_tile(p.sched, pos);
+    int l = sched_logical(p.sched, pos), part = 0;
+    if constexpr (SPLIT) {   // the split index goes slowest: what runs side by side on a die works on the same range of K
+      const int n_tiles = p.sched.nbm * p.sched.nbn;
+      part = l / n_tiles;
+      l -= part * n_tiles;
+    }
+    int tile = sched_tile_at(p.sched, l);
     int bm = tile / p.sched.nbn, bn = tile - bm * p.sched.nbn;
     int row_lo = bm * Cfg::BM, col_lo = bn * Cfg::BN;
     int rows = min(Cfg::BM, p.M - row_lo), cols = min(Cfg::BN, p.N - col_lo);
@@ -76,7 +95,8 @@ __global__ void __launch_bounds__(Cfg::NTHREADS) ag_gemm_kernel(const AgGemmPara
     const int clo = row_lo / M_per_channel, chi = (row_lo + rows - 1) / M_per_channel;
     if (p.do_wait == 1) {
       unsigned long long mask = ((chi - clo + 1 >= 64) ? ~0ull : ((1ull << (chi - clo + 1)) - 1)) << clo;
-      consumer_wait_or_produce<8>(p.prod, mask, tid, Cfg::NTHREADS, &s_ticket);
+      if (p.share) consumer_wait_shared<8>(p.prod, mask, tid, Cfg::NTHREADS, s_share);
+      else consumer_wait_or_produce<8>(p.prod, mask, tid, Cfg::NTHREADS, &s_ticket);
     } else if (p.do_wait == 2) {
       // flags raised by somebody else (no ticket queue): plain wait
       if (tid == 0)
@@ -86,7 +106,12 @@ __global__ void __launch_bounds__(Cfg::NTHREADS) ag_gemm_kernel(const AgGemmPara
     Out out;
     if constexpr (GATED) out = Out{p.c + (long)row_lo * (p.N / 2) + col_lo / 2, p.N / 2, p.act};
     else out = Out{p.c + (long)row_lo * p.N + col_lo, p.N};
-    if (p.prod.k_chunks > 1 && p.do_wait) {
+    if constexpr (SPLIT) {
+      const int k_lo = part * p.split_steps * Cfg::BK, k_n = min(p.K - k_lo, p.split_steps * Cfg::BK);
+      gemm_tile<Cfg>(p.prod.gathered + (long)row_lo * p.K + k_lo, p.K, nullptr, 1, p.b + (long)k_lo * p.N + col_lo, p.N, out, rows, cols, k_n, smem,
+                     NoKWait{}, NoHook{},
+                     SplitK<Cfg>{p.slots + (long)tile * p.splits * SplitK<Cfg>::SLOT, p.counts + tile, p.prod.epoch * (unsigned)p.splits - 1u, p.splits, part, &s_ticket});
+    } else if (p.prod.k_chunks > 1 && p.do_wait) {
       gemm_tile<Cfg>(p.prod.gathered + (long)row_lo * p.K, p.K, nullptr, 1, p.b + col_lo, p.N, out, rows, cols, p.K, smem,
                      ChunkWait{p.prod.flags, p.prod.k_chunks, p.K / Cfg::BK / p.prod.k_chunks, clo, chi, p.prod.wait_target, p.prod.ctl});
     } else {
@@ -369,6 +394,37 @@ int fail(int code, const char* fmt, ...) {
 // the communication side, overlaps the remaining GEMM tiles and only a push is left at the end).
 static int rs_first_rank(const tl_config& c) { return c.tile_order >= TL_ORDER_OWN_FIRST ? c.rank : (c.rank + 1) % c.world_size; }
 
+// Time of a GEMM on the two square tile shapes, in microseconds, for choosing between them and for the number of
+// workgroups that share a tile: every round of workgroups costs the fixed part of a tile (first loads, epilogue, store)
+// and its K steps of 64, and a step takes the longer the more compute units are busy (they share the memory side and the
+// power limit).  Fitted to timings of this kernel without communication: 256x256 with K = 8192 takes 123 / 156 / 214 us
+// on 1 / 128 / 256 compute units, K = 1024 24 / 29 / 37 us; 128x128 40 / 52 / 66 us on 1 / 112 / 256, 10 / 12 / 14 us.
+static double tile_rounds_us(bool large, long workgroups, double steps, int cus) {
+  auto round = [&](double busy) { return large ? 6.5 + steps * (0.92 + 0.70 * busy) : 3.5 + steps * (0.30 + 0.19 * busy); };
+  const long full = workgroups / cus, rest = workgroups % cus;
+  return full * round(1.0) + (rest ? round((double)rest / cus) : 0.0);
+}
+
+constexpr int kMaxSplits = 8;
+// Workgroups that share a 128x128 tile along K.  Only where they all run at once, and only down to 1024 of K each: below
+// that the fixed part of a tile is most of its time.  What the last one adds for the others -- its own slot's way to
+// memory and the count, then the slots it reads -- is about 2 us + 0.8 us a slot.
+static int choose_splits(long tiles, int K, int cus, double* us) {
+  int best = 1;
+  *us = tile_rounds_us(false, tiles, K / 64.0, cus);
+  for (int S = 2; S <= kMaxSplits && tiles * S <= cus && K >= 1024 * S; S++) {
+    const double t = tile_rounds_us(false, tiles * S, K / 64.0 / S, cus) + 2.0 + 0.8 * S;
+    if (t < *us) { *us = t; best = S; }
+  }
+  return best;
+}
+
+// Scratch of a call whose tiles are shared (after the first 256 bytes of the workspace): counters, then slots.
+static size_t split_count_bytes(const Resolved& r) { return ((size_t)r.n_tiles * sizeof(unsigned) + 255) / 256 * 256; }
+static size_t split_bytes(const Resolved& r) {
+  return r.splits > 1 ? split_count_bytes(r) + (size_t)r.n_tiles * r.splits * r.tile_m * r.tile_n * sizeof(float) : 0;
+}
+
 int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, bool paired_columns) {
   const tl_config& c = ctx->cfg;
   if (M <= 0 || N <= 0 || K <= 0) return fail(TL_ERR_INVALID_ARG, "M, N, K must be positive (got %d, %d, %d)", M, N, K);
@@ -379,14 +435,19 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
   if (paired_columns && N % 64) return fail(TL_ERR_UNSUPPORTED_SHAPE, "gate and up columns alternate in blocks of 32: 2F=%d must be a multiple of 64", N);
   memset(r, 0, sizeof *r);
   // ---- compute tile
-  int v = -1;
+  int v = -1, splits = 1;
   if (c.tile_m || c.tile_n) {
     for (int i = 0; i < TILE_VARIANTS; i++)
       if (kTileM[i] == c.tile_m && kTileN[i] == c.tile_n) v = i;
     if (v < 0) return fail(TL_ERR_UNSUPPORTED_SHAPE, "compute tile %dx%d is not one of 256x256, 256x224, 128x128", c.tile_m, c.tile_n);
-  } else if ((long)M * N <= 1024L * 1024L) {
-    v = TILE_128x128;
   } else {
+    const long n_small = (long)ceil_div(M, 128) * ceil_div(N, 128), n_large = (long)ceil_div(M, 256) * ceil_div(N, 256);
+    double us_small = tile_rounds_us(false, n_small, K / 64.0, ctx->num_cus);
+    if (op == TL_OP_AG_GEMM) splits = choose_splits(n_small, K, ctx->num_cus, &us_small);
+    if (us_small < tile_rounds_us(true, n_large, K / 64.0, ctx->num_cus)) v = TILE_128x128;
+    else splits = 1;
+  }
+  if (v < 0) {
     // 256x256 unless the 224-wide tile divides N and fills the last round of workgroups much better: its wave tile
     // (32x224) reads more LDS bytes per flop and the kernel takes all 256 vector registers, which keeps side-kernel
     // waves off its compute units; measured on 8192x3584x8192, 448 tiles of 256x256 (1.75 rounds) beat 512 of 256x224
@@ -413,6 +474,7 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
   if (c.compute_workgroups == 0 && c.comm_mode == TL_COMM_STREAM && op == TL_OP_AG_GEMM && G > 32) G -= 16;
   if (G > r->n_tiles) G = r->n_tiles;
   r->G = G;
+  r->splits = c.compute_workgroups == 0 && c.comm_mode != TL_COMM_STREAM && G == r->n_tiles ? splits : 1;
   {
     // group of row blocks walked together: a power of two that keeps a group inside one rank's rows
     int per_rank = (r->nbm % R == 0) ? r->nbm / R : r->nbm;
@@ -436,8 +498,10 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     if ((long)R * C > 64) return fail(TL_ERR_UNSUPPORTED_SHAPE, "world size %d x channels per rank %d = %ld channels; at most 64 are supported", R, C, (long)R * C);
     if (r->rows_per_rank % C) return fail(TL_ERR_UNSUPPORTED_SHAPE, "channels per rank %d must divide M/R=%d", C, r->rows_per_rank);
     r->rows_per_channel = r->rows_per_rank / C;
-    int Tm_p = c.comm_tile_m;
-    if (Tm_p == 0) {
+    int Tm_p = c.comm_tile_m, Tn_p = c.comm_tile_n ? c.comm_tile_n : K;
+    if (Tm_p == 0 && c.link_gbps == 0 && c.comm_tile_n == 0 && c.ag_k_chunks < 2) {
+      choose_producer_tile(r->rows_per_channel, K, (long)M * K * 2, ctx->num_cus, &Tm_p, &Tn_p);
+    } else if (Tm_p == 0) {
       Tm_p = r->rows_per_channel;
       // small row tiles: many producer tiles per channel keeps all copy workgroups busy.  With simulated links only the
       // tiles that are due are being copied, a handful at a time and each by one workgroup at the pace of its own memory
@@ -448,7 +512,6 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     }
     if (Tm_p <= 0 || r->rows_per_channel % Tm_p)
       return fail(TL_ERR_UNSUPPORTED_SHAPE, "producer row tile %d must divide the rows per channel M/(R*C)=%d", Tm_p, r->rows_per_channel);
-    int Tn_p = c.comm_tile_n ? c.comm_tile_n : K;
     if (Tn_p <= 0 || K % Tn_p || Tn_p % 8) return fail(TL_ERR_UNSUPPORTED_SHAPE, "producer column tile %d must divide K=%d and be a multiple of 8", Tn_p, K);
     // K chunks: only where the producers are certain to be resident beside the GEMM workgroups (a tile that is already
     // in its K loop waits without helping them), i.e. the 256x256 tile with in-kernel or side-kernel producers
@@ -472,6 +535,19 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     r->n_ptm = M / Tm_p;
     r->n_ptn = K / Tn_p;
     r->expected = r->k_chunks > 1 ? r->rows_per_channel / Tm_p : (r->rows_per_channel / Tm_p) * r->n_ptn;
+    // The gather's producers as part of the GEMM launch, unless their number is given or links are simulated: up to 64
+    // workgroups in front of the GEMM's -- on compute units its only round leaves free if there are some --, no more than
+    // there are tiles to copy for two each (the waiting GEMM workgroups copy too, and every one that asks in vain holds up
+    // the queue).  As a kernel of their own they start 6 us behind the GEMM, which waits for them: measured, fused,
+    // [8192,8192] x [8192,3584] 440 -> 420 us, [8192,4096] x [4096,1376] 128 -> 120 us.
+    r->fold = 0;
+    if (c.comm_workgroups == 0 && c.link_gbps == 0 && (c.comm_mode == TL_COMM_WAVES || c.comm_mode == TL_COMM_SIDE_KERNEL)) {
+      r->fold = 1;
+      const int idle = (ctx->num_cus - G * r->splits) / kXcds * kXcds, work = ceil_div(r->n_ptm * r->n_ptn, 2 * kXcds) * kXcds;
+      const int n = idle >= 16 && idle < 64 ? idle : 64;
+      r->n_comm = n < work ? n : work;
+      if (r->k_chunks == 1 && r->n_tiles * r->splits <= ctx->num_cus) r->n_comm = idle < work ? idle : work;   // shares: as many as there is room for
+    }
     r->first_block = 0;
     if (c.tile_order != TL_ORDER_NATURAL) {
       if (r->nbm % R == 0) r->first_block = c.rank * (r->nbm / R);
@@ -513,6 +589,9 @@ static Sched make_sched(const tl_ctx* ctx, const Resolved& r, int op) {
 }
 
 static int launch_ag_gemm(int variant, const AgGemmParams& p, int grid, hipStream_t s) {
+  if (p.splits > 1)
+    return p.act ? launch_fused<Cfg128x128>(ag_gemm_kernel<Cfg128x128, true, true>, p, grid, s)
+                 : launch_fused<Cfg128x128>(ag_gemm_kernel<Cfg128x128, false, true>, p, grid, s);
   if (p.act) {
     if (variant == TILE_256x256) return launch_fused<Cfg256x256>(ag_gemm_kernel<Cfg256x256, true>, p, grid, s);
     if (variant == TILE_128x128) return launch_fused<Cfg128x128>(ag_gemm_kernel<Cfg128x128, true>, p, grid, s);
@@ -613,6 +692,10 @@ int tl_query_workspace(const tl_ctx* ctx, int op, const long long* dims, size_t*
     *ws_bytes = 256;  // status word (+ padding)
     if (op == TL_OP_AG_GEMM) {
       *n_flags = (size_t)ctx->cfg.world_size * ctx->cfg.channels_per_rank * r.k_chunks;
+      size_t scratch = split_bytes(r);
+      Resolved g;   // the gated form may choose another tile
+      if (dims[1] % 64 == 0 && resolve_dense(ctx, op, (int)dims[0], (int)dims[1], (int)dims[2], &g, true) == TL_OK && split_bytes(g) > scratch) scratch = split_bytes(g);
+      *ws_bytes += scratch;
     } else {
       size_t tiles_per_seg = (size_t)(r.rows_per_rank / r.Tm_p) * r.n_ptn;
       *n_flags = (size_t)r.n_ptm * r.n_ptn + 2 * (size_t)ctx->cfg.world_size * tiles_per_seg;
@@ -723,6 +806,7 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
       if (q != cfg.rank && (!peer_slots[q] || !aligned16(peer_slots[q]))) return fail(TL_ERR_INVALID_ARG, "tl_ag_gemm_push: peer_slots[%d] is null or misaligned", q);
       p.prod.peer_slots[q] = (bf16_t*)peer_slots[q];
     }
+    if (r.fold && r.n_comm < 64) r.n_comm = 64;   // pushes are nobody's wait: the producer workgroups do them
     p.prod.n_out = (r.rows_per_rank / r.Tm_p) * r.n_ptn * (R - 1);
     p.prod.pushed = flags + (size_t)R * cfg.channels_per_rank * r.k_chunks;
     p.prod.ticket_end = epoch * (unsigned)(r.n_ptm * r.n_ptn + p.prod.n_out);
@@ -732,9 +816,23 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
   p.M = M; p.N = N; p.K = K;
   p.act = act;
   p.sched = make_sched(ctx, r, TL_OP_AG_GEMM);
+  int G = r.G;
+  p.splits = 1;
+  if (r.splits > 1 && ws_bytes >= 256 + split_bytes(r)) {   // (a smaller workspace, as the static entry point's: whole tiles)
+    const int steps = ceil_div(K, Cfg128x128::BK);
+    p.splits = r.splits;
+    p.split_steps = ceil_div(steps, r.splits);
+    p.counts = (unsigned*)((char*)workspace + 256);
+    p.slots = (float*)((char*)workspace + 256 + split_count_bytes(r));
+    p.sched.n_tiles *= r.splits;
+    p.sched.G *= r.splits;
+    G *= r.splits;
+  }
   hipStream_t cs = (hipStream_t)compute_stream, ms = (hipStream_t)comm_stream;
 
   const bool alone = cfg.comm_alone != 0;  // communication side only (timing)
+  // shares: the whole launch has to fit on the chip at once (and nothing but the gather itself is to be done)
+  const bool share = r.fold && !peer_slots && G + r.n_comm <= ctx->num_cus && (r.k_chunks == 1 || r.n_comm >= 16);
   if (r.k_chunks > 1 && cfg.comm_mode != TL_COMM_WAVES && cfg.comm_mode != TL_COMM_SIDE_KERNEL) r.k_chunks = 1;
   if (alone && (cfg.comm_mode == TL_COMM_NONE || cfg.comm_mode == TL_COMM_EXTERNAL))
     return fail(TL_ERR_INVALID_ARG, "tl_ag_gemm: comm_alone needs a comm_mode in which the library runs a producer");
@@ -742,23 +840,30 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
   switch (cfg.comm_mode) {
     case TL_COMM_NONE:
       p.n_comm = 0; p.do_wait = 0;
-      return launch_ag_gemm(r.variant, p, r.G, cs);
+      return launch_ag_gemm(r.variant, p, G, cs);
     case TL_COMM_WAVES:
       p.n_comm = r.n_comm; p.do_wait = 1;
       p.prod.wait_target = epoch * (unsigned)r.expected;
-      return launch_ag_gemm(r.variant, p, alone ? r.n_comm : r.G + r.n_comm, cs);
+      p.share = share && !alone;
+      return launch_ag_gemm(r.variant, p, alone ? r.n_comm : G + r.n_comm, cs);
     case TL_COMM_EXTERNAL:
       p.n_comm = 0; p.do_wait = 2;
       p.prod.wait_target = epoch * (unsigned)r.expected;
-      return launch_ag_gemm(r.variant, p, r.G, cs);
+      return launch_ag_gemm(r.variant, p, G, cs);
     case TL_COMM_SIDE_KERNEL: {
+      if (r.fold && !alone) {   // (on ms alone nothing of the gather may be relied on in this binding either way: GEMM workgroups copy too)
+        p.n_comm = r.n_comm; p.do_wait = 1;
+        p.prod.wait_target = epoch * (unsigned)r.expected;
+        p.share = share;
+        return launch_ag_gemm(r.variant, p, G + r.n_comm, cs);
+      }
       // The producer is enqueued first: it waits for nothing, so even if both streams end up on one
       // hardware queue the worst case is that the two kernels run one after the other.
       p.n_comm = 0; p.do_wait = 1;
       p.prod.wait_target = epoch * (unsigned)r.expected;
-      hipLaunchKernelGGL(ag_producer_kernel, dim3(r.n_comm), dim3(256), 0, ms, p.prod);
+      hipLaunchKernelGGL(ag_producer_kernel, dim3(r.fold ? 128 : r.n_comm), dim3(256), 0, ms, p.prod);
       TL_HIP(hipGetLastError());
-      return alone ? TL_OK : launch_ag_gemm(r.variant, p, r.G, cs);
+      return alone ? TL_OK : launch_ag_gemm(r.variant, p, G, cs);
     }
     case TL_COMM_STREAM:
     case TL_COMM_COPY_ENGINE: {
@@ -775,7 +880,7 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
         hipLaunchKernelGGL(notify_kernel, dim3((cfg.channels_per_rank + 63) / 64), dim3(64), 0, ms, flags + q * cfg.channels_per_rank, cfg.channels_per_rank, 1u);
         TL_HIP(hipGetLastError());
       }
-      return alone ? TL_OK : launch_ag_gemm(r.variant, p, r.G, cs);
+      return alone ? TL_OK : launch_ag_gemm(r.variant, p, G, cs);
     }
   }
   return fail(TL_ERR_INVALID_ARG, "tl_ag_gemm: unknown comm_mode");

@@ -278,8 +278,8 @@ __host__ __device__ inline void colgroup_tile(int l, int nbm, int nbn, int gb, i
   *bn = g * gb + (within - *bm * gsz);
 }
 
-__host__ __device__ inline int sched_tile(const Sched& s, int p) {
-  int l = sched_logical(s, p);
+// Output tile at logical index l.
+__host__ __device__ inline int sched_tile_at(const Sched& s, int l) {
   int per_group = s.group_m * s.nbn;
   int g = l / per_group, within = l - g * per_group;
   int gsz = s.nbm - g * s.group_m;  // row blocks in this group (the last group may be short)
@@ -297,6 +297,8 @@ __host__ __device__ inline int sched_tile(const Sched& s, int p) {
   if (bm >= s.nbm) bm -= s.nbm;
   return bm * s.nbn + bn;
 }
+
+__host__ __device__ inline int sched_tile(const Sched& s, int p) { return sched_tile_at(s, sched_logical(s, p)); }
 
 // ---------------------------------------------------------------------------------------
 // Tile movers of the communication side: copy_tile (tile_push_data / tile_pull_data / rank_copy_data)
@@ -370,6 +372,27 @@ __device__ __forceinline__ void buf_store16(u32x4 v, rsrc_t r, unsigned lane_off
 template <int DEPTH = 8>  // loads in flight per lane
 __device__ __forceinline__ void copy_tile(const bf16_t* __restrict__ src, long src_ld, bf16_t* __restrict__ dst, long dst_ld,
                                           int rows, int cols, int tid, int nthreads) {
+  if (src_ld == cols && dst_ld == cols) {   // whole rows: one contiguous piece, whatever the number of chunks per row
+    const int total = rows * (cols >> 3), step = nthreads * 16;
+    const rsrc_t rs = tile_rsrc(src, cols, rows, cols), rd = tile_rsrc(dst, cols, rows, cols);
+    const unsigned o = (unsigned)tid * 16u;
+    int at = 0;   // chunk index of lane 0
+    for (; at + DEPTH * nthreads <= total; at += DEPTH * nthreads) {
+      u32x4 v[DEPTH];
+#pragma unroll
+      for (int u = 0; u < DEPTH; u++) v[u] = buf_load16(rs, o, (unsigned)at * 16u + (unsigned)(u * step));
+#pragma unroll
+      for (int u = 0; u < DEPTH; u++) buf_store16(v[u], rd, o, (unsigned)at * 16u + (unsigned)(u * step));
+    }
+    for (; at + 2 * nthreads <= total; at += 2 * nthreads) {
+      u32x4 v0 = buf_load16(rs, o, (unsigned)at * 16u), v1 = buf_load16(rs, o, (unsigned)at * 16u + (unsigned)step);
+      buf_store16(v0, rd, o, (unsigned)at * 16u);
+      buf_store16(v1, rd, o, (unsigned)at * 16u + (unsigned)step);
+    }
+    for (; at < total; at += nthreads)   // at most one full step, then the partial one
+      if (at + tid < total) buf_store16(buf_load16(rs, o, (unsigned)at * 16u), rd, o, (unsigned)at * 16u);
+    return;
+  }
   const int cpr = cols >> 3;  // 16-byte chunks per row
   const unsigned sld = (unsigned)src_ld * 2u, dld = (unsigned)dst_ld * 2u;
   const TileSteps ts = tile_steps(rows, cpr, tid, nthreads);

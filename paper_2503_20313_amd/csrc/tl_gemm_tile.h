@@ -120,6 +120,76 @@ struct NoHook {
   __device__ __forceinline__ void run() const {}
 };
 
+// Hook of gemm_tile between the K loop and the epilogue, for tiles whose K range is shared by several workgroups: combines
+// the partial accumulators; false: another workgroup finishes this tile, there is nothing to store here.
+struct NoSplit {
+  static constexpr bool ENABLED = false;
+};
+
+// Split K: workgroup `s` of the S workgroups that share one output tile has multiplied its part of the K range.  Each
+// leaves its fp32 accumulators in its slot of the tile's scratch, in accumulator order (a lane's 16-byte pieces, so every
+// store covers 1 KiB), written through to device scope, and counts itself in; the one that finds all others counted
+// adds the slots in the order s = 0, 1, .. (its own from registers: the sum does not depend on who comes last) and goes
+// on to the epilogue.  Nobody waits for anybody.  The slots' lines are read by no one before the count says they are
+// complete, so the fence after the count leaves the caches alone (see TL_ACQ_SCOPE).
+template <class Cfg>
+struct SplitK {
+  static constexpr bool ENABLED = true;
+  float* slots;        // the tile's S slots of BM x BN floats
+  unsigned* count;     // grows by S per call
+  unsigned last;       // its value (before the add) that the last workgroup of this call finds
+  int S, s;
+  int* s_old;          // an int in LDS
+  static constexpr int SLOT = Cfg::BM * Cfg::BN;
+  __device__ __forceinline__ bool combine(floatx16 (&acc)[Cfg::MT][Cfg::NT]) const {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long wave_off = (long)wave * (Cfg::MT * Cfg::NT * 16 * 64);
+    const char* base = (const char*)uniform64((unsigned long long)(slots + (long)s * SLOT + wave_off));
+#pragma unroll
+    for (int mt = 0; mt < Cfg::MT; mt++)
+#pragma unroll
+      for (int nt = 0; nt < Cfg::NT; nt++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          floatx4 v = {acc[mt][nt][g * 4], acc[mt][nt][g * 4 + 1], acc[mt][nt][g * 4 + 2], acc[mt][nt][g * 4 + 3]};
+          store16_device_scope(base + ((mt * Cfg::NT + nt) * 4 + g) * 1024, (unsigned)lane * 16u, __builtin_bit_cast(u32x4, v));
+        }
+    wait_all_vmem();
+    __syncthreads();   // every wave's part of the slot is where every die sees it
+    if (wave == 0) *s_old = (int)lane0_fetch_add(count, 1u);
+    __syncthreads();
+    if ((unsigned)__builtin_amdgcn_readfirstlane(*s_old) != last) return false;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, TL_ACQ_SCOPE);
+    floatx16 sum[Cfg::MT][Cfg::NT];
+#pragma unroll
+    for (int mt = 0; mt < Cfg::MT; mt++)
+#pragma unroll
+      for (int nt = 0; nt < Cfg::NT; nt++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) sum[mt][nt][e] = 0.f;
+    for (int q = 0; q < S; q++) {
+      const floatx4* src = (const floatx4*)(slots + (long)q * SLOT + wave_off) + lane;
+#pragma unroll
+      for (int mt = 0; mt < Cfg::MT; mt++)
+#pragma unroll
+        for (int nt = 0; nt < Cfg::NT; nt++)
+#pragma unroll
+          for (int g = 0; g < 4; g++) {
+            floatx4 v;
+            if (q == s) v = floatx4{acc[mt][nt][g * 4], acc[mt][nt][g * 4 + 1], acc[mt][nt][g * 4 + 2], acc[mt][nt][g * 4 + 3]};
+            else v = src[((mt * Cfg::NT + nt) * 4 + g) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; e++) sum[mt][nt][g * 4 + e] += v[e];
+          }
+    }
+#pragma unroll
+    for (int mt = 0; mt < Cfg::MT; mt++)
+#pragma unroll
+      for (int nt = 0; nt < Cfg::NT; nt++) acc[mt][nt] = sum[mt][nt];
+    return true;
+  }
+};
+
 // Output of a GEMM whose B holds a gate and an up projection side by side, 32 columns of the one, then the same 32
 // features of the other (so that the two values of a feature sit in the same lane, in neighbouring 32x32 accumulator
 // blocks): the tile stores act(gate) * up, half as many columns as it computes (the activation between the two halves
@@ -162,10 +232,10 @@ struct GatedRows {
 // offset fixed for the whole tile).  The loop body is left with no vector-ALU instruction besides the matrix ones:
 // measured, every vector instruction taken out of this loop shortened it, in cycles and -- on a chip that runs the
 // matrix cores at its power limit -- in clock.
-template <class Cfg, class Out, class KW = NoKWait, class Hook = NoHook>
+template <class Cfg, class Out, class KW = NoKWait, class Hook = NoHook, class Split = NoSplit>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ a, long lda, const int* __restrict__ a_rows, int a_div,
                                           const bf16_t* __restrict__ b, long ldb, const Out& out, int rows, int cols, int K,
-                                          char* smem, const KW& kw = KW{}, const Hook& hook = Hook{}) {
+                                          char* smem, const KW& kw = KW{}, const Hook& hook = Hook{}, const Split& split = Split{}) {
   constexpr int NS = Cfg::NS, SL = Cfg::SL, LPW = Cfg::LPW;
   constexpr int A_REGION = NS * Cfg::A_BYTES;   // the B stages start here
   const int tid = threadIdx.x, lane = tid & 63;
@@ -385,6 +455,9 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ a, long lda
   }
   slice(integral_constant<int, (SL - 1) & 1>{}, integral_constant<int, -1>{}, no{}, 0, integral_constant<int, 0>{}, no{}, no{}, 0);
   __syncthreads();  // all operand reads of this tile are complete: LDS is free for the epilogue
+  if constexpr (Split::ENABLED) {
+    if (!split.combine(acc)) return;   // (uniform) the workgroup that comes last stores the tile
+  }
 
   // ---- epilogue.  Accumulator register e of lane l holds C[row = l%32][col = (e/4)*8 + (l/32)*4 + e%4] of its 32x32
   // block: stored from there, every store instruction would touch 32 rows with 16 bytes each.  Instead the wave

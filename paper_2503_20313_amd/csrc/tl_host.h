@@ -36,6 +36,8 @@ struct Resolved {
   int variant, tile_m, tile_n;
   int nbm, nbn, n_tiles;
   int G, n_comm;
+  int fold;              // AG+GEMM: TL_COMM_SIDE_KERNEL runs its producers as workgroups of the GEMM launch
+  int splits;            // AG+GEMM: workgroups that share a tile along K (1: none)
   int Tm_p, Tn_p;        // producer / reduce tile
   int n_ptm, n_ptn;      // producer or reduce tiles along rows / columns
   int rows_per_rank, rows_per_channel;
@@ -75,6 +77,29 @@ inline WaitCtl make_ctl(const tl_ctx* ctx, void* workspace) {
   c.timeout = (unsigned long long)ctx->cfg.spin_timeout_us * 100ull;  // 100 MHz wall clock
   c.strict = 0;
   return c;
+}
+
+// Producer tile of a gather of `rows` x ld elements per channel, `total` bytes in all, with `workers` workgroups to copy it
+// (the GEMM's waiting ones among them): as close as the divisors allow to one tile for each, or two where that leaves more
+// than 64 KiB, within 16 KiB and 256 KiB.  A hand-out is several trips to memory -- claim, copy, notification, 5-8 us in
+// all --, so a small gather is done in one hand-out each.  Whole rows if possible (one contiguous piece); rows that have no
+// fitting divisor are cut along the columns instead, in pieces of at least a cache line.
+inline void choose_producer_tile(int rows, int ld, long total, int workers, int* Tm, int* Tn) {
+  long want = total / workers;
+  if (want > 65536) want = want / 2 > 65536 ? want / 2 : 65536;
+  want = want < 16384 ? 16384 : (want > 262144 ? 262144 : want);
+  auto off = [&](long bytes) { return bytes > want ? (double)bytes / want : (double)want / bytes; };
+  double best = 1e30;
+  for (int tm = 1; tm <= rows; tm++) {
+    if (rows % tm) continue;
+    int tn = ld;
+    for (double cost = 1.0;; cost = 1.5) {   // (a cut tile has to be half as far off again before a whole-row one is taken)
+      const double c = cost * off(2L * tm * tn);
+      if (c < best) { best = c; *Tm = tm; *Tn = tn; }
+      if (tn % 16 || tn / 2 < 64) break;
+      tn /= 2;
+    }
+  }
 }
 
 // Launches a kernel that uses Cfg::LDS_BYTES of dynamic LDS.
