@@ -20,155 +20,236 @@ constexpr int kRouteThreads = 1024;
 // Routing, step 1: per token, the k largest gate logits (ties -> lower expert index, listed by
 // descending logit) and their softmax weights (over all E experts, renormalised over the k
 // selected if asked).  One thread per token.
+//
+// Bound by latency: few threads, a long chain each.  The token's logits are read once, all loads in flight together, and
+// stay in registers (EMAX >= E of them); read anew for every pass over the experts, as a loop over memory, 512 tokens x 32
+// experts, top-5, took 39 us and the sort 13 us (now one launch of 16 us, see below), 8192 tokens, top-2, 51 us (now 10 us).
 // ======================================================================================
-__global__ void moe_topk_kernel(const float* __restrict__ logits, int T, int E, int topk, int renormalize, int* __restrict__ topk_ids,
-                                float* __restrict__ topk_w) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= T) return;
-  const float* row = logits + (long)t * E;
-  float mx = row[0];
-  for (int e = 1; e < E; e++) mx = fmaxf(mx, row[e]);
+template <int EMAX>
+__device__ __forceinline__ void topk_of_token(const float* __restrict__ row, int E, int topk, int renormalize, int* __restrict__ ids, float* __restrict__ weights) {
+  float v[EMAX];
+  if (E == EMAX && ((uintptr_t)row & 15) == 0) {
+#pragma unroll
+    for (int e = 0; e < EMAX; e += 4) {
+      const floatx4 q = *(const floatx4*)(row + e);
+#pragma unroll
+      for (int i = 0; i < 4; i++) v[e + i] = q[i];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EMAX; e++) v[e] = e < E ? row[e] : -INFINITY;
+  }
+  float mx = v[0];
+#pragma unroll
+  for (int e = 1; e < EMAX; e++)
+    if (e < E) mx = fmaxf(mx, v[e]);
   float denom = 0.f;
-  for (int e = 0; e < E; e++) denom += expf(row[e] - mx);
+#pragma unroll
+  for (int e = 0; e < EMAX; e++)
+    if (e < E) denom += expf(v[e] - mx);
   unsigned long long taken = 0;
   float w[kMaxTopk];
   float wsum = 0.f;
-  for (int j = 0; j < topk; j++) {
+#pragma unroll
+  for (int j = 0; j < kMaxTopk; j++) {
+    if (j >= topk) break;
     int best = -1;
     float bv = 0.f;
-    for (int e = 0; e < E; e++) {
-      if ((taken >> e) & 1) continue;
-      float v = row[e];
-      if (best < 0 || v > bv) { best = e; bv = v; }  // strict >: the lower index wins a tie
-    }
+#pragma unroll
+    for (int e = 0; e < EMAX; e++)
+      if (e < E && !((taken >> e) & 1) && (best < 0 || v[e] > bv)) { best = e; bv = v[e]; }  // strict >: the lower index wins a tie
     taken |= 1ull << best;
-    topk_ids[(long)t * topk + j] = best;
+    ids[j] = best;
     w[j] = expf(bv - mx) / denom;
     wsum += w[j];
   }
-  for (int j = 0; j < topk; j++) topk_w[(long)t * topk + j] = renormalize ? w[j] / wsum : w[j];
+#pragma unroll
+  for (int j = 0; j < kMaxTopk; j++)
+    if (j < topk) weights[j] = renormalize ? w[j] / wsum : w[j];
+}
+
+// (blocks of one wave: 8192 tokens are then 128 of them, on as many compute units)
+template <int EMAX>
+__global__ void __launch_bounds__(64) moe_topk_kernel(const float* __restrict__ logits, int T, int E, int topk, int renormalize, int* __restrict__ topk_ids,
+                                                      float* __restrict__ topk_w) {
+  const int t = blockIdx.x * 64 + threadIdx.x;
+  if (t < T) topk_of_token<EMAX>(logits + (long)t * E, E, topk, renormalize, topk_ids + (long)t * topk, topk_w + (long)t * topk);
 }
 
 // ======================================================================================
 // Routing, step 2 (one workgroup of 16 waves): stable counting sort of the routed rows by expert, expert
 // offsets, and the tile tables.  Wave w owns a contiguous range of rows and walks it 64 rows at a time; inside
 // a step the lanes that route to the same expert are found with one ballot per bit of the expert index, which
-// gives every row its rank among them.  Pass A counts rows per (wave, expert); a scan turns the counts into the
-// position where each wave's rows of each expert start; pass B places the rows (stable: waves, steps and lanes
-// are in row order) and ORs each row's AllGather channel into its tile's mask.
+// gives every row its rank among them.  Pass A counts rows per (wave, expert); a scan by wave 0 (lane = expert) turns the
+// counts into the position where each wave's rows of each expert start; pass B places the rows (stable: waves, steps and
+// lanes are in row order) and ORs each row's AllGather channel into its tile's mask, from which the span of source ranks
+// follows at the end.
+//
+// Bound by latency as well: the expert indices are read kRouteAhead steps at a time, the divisions of the inner loop are
+// multiplications, and what used to be loops of one thread over the experts is a scan.  16384 rows, 32 experts: 50 -> 30 us.
+// With EMAX > 0 the workgroup does step 1 for up to kRouteThreads tokens first: a small call then is one launch.
 // ======================================================================================
 constexpr int kRouteWaves = kRouteThreads / 64;
-constexpr int kLdsTiles = 2048;  // tile tables are assembled in LDS up to this many tiles, else in global memory
+constexpr int kLdsTiles = 2048;  // channel masks are collected in LDS up to this many tiles, else in global memory
+constexpr int kRouteAhead = 8;
 
-__device__ __forceinline__ unsigned long long same_expert_lanes(int e, bool valid) {
+// n / d for 0 <= n < 2^31 as a multiplication by a 32-bit reciprocal (round-up method: m = floor(2^32 (2^l - d) / d) + 1
+// with l = ceil(log2 d), n / d = (mulhi(m, n) + n) >> l).
+struct FastDiv {
+  unsigned mul, shift;
+  __device__ __forceinline__ unsigned div(unsigned n) const { return (__umulhi(mul, n) + n) >> shift; }
+};
+static FastDiv make_fast_div(unsigned d) {
+  FastDiv f;
+  f.shift = 0;
+  while (f.shift < 31 && (1u << f.shift) < d) f.shift++;
+  f.mul = (unsigned)((((1ull << f.shift) - d) << 32) / d + 1);
+  return f;
+}
+
+__device__ __forceinline__ unsigned long long same_expert_lanes(int e, bool valid, int E) {
   unsigned long long same = __builtin_amdgcn_ballot_w64(valid);
 #pragma unroll
   for (int b = 0; b < 6; b++) {  // kMaxExperts = 64
+    if ((1 << b) >= E) break;
     unsigned long long bal = __builtin_amdgcn_ballot_w64(valid && ((e >> b) & 1));
     same &= ((e >> b) & 1) ? bal : ~bal;
   }
   return same;
 }
 
-__global__ void __launch_bounds__(kRouteThreads) moe_sort_kernel(const int* __restrict__ topk_ids, int n_rows, int E, int topk, int T, int R, int C,
-                                                                 int Tm, int* __restrict__ expert_offsets, int* __restrict__ sorted_row,
-                                                                 int* __restrict__ tile_tables, int* __restrict__ n_tiles) {
+struct RouteParams {
+  const float* logits;      // used with EMAX > 0 only
+  int* topk_ids;            // [n_rows]; written with EMAX > 0
+  float* topk_w;
+  int n_rows, E, topk, T, renormalize;
+  int C;                    // AllGather channels per rank
+  int Tm;
+  FastDiv by_channel;       // rows per channel: tokens per channel x topk
+  FastDiv by_tile;          // Tm
+  int* expert_offsets;
+  int* sorted_row;
+  int* tile_tables;
+  int* n_tiles;
+};
+
+template <int EMAX>
+__global__ void __launch_bounds__(kRouteThreads) moe_sort_kernel(const RouteParams p) {
   __shared__ int s_cnt[kRouteWaves][kMaxExperts];
   __shared__ int s_off[kMaxExperts + 1], s_tbase[kMaxExperts + 1];
   __shared__ unsigned s_mlo[kLdsTiles], s_mhi[kLdsTiles];
-  __shared__ int s_rmin[kLdsTiles], s_rmax[kLdsTiles];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_rows = p.n_rows, E = p.E, Tm = p.Tm;
   const int chunk = ((n_rows + kRouteWaves - 1) / kRouteWaves + 63) / 64 * 64;
   const int lo = min(wave * chunk, n_rows), hi = min(lo + chunk, n_rows);
   const unsigned long long below = (1ull << lane) - 1;
-  for (int i = tid; i < kRouteWaves * kMaxExperts; i += kRouteThreads) (&s_cnt[0][0])[i] = 0;
-  __syncthreads();
+  if constexpr (EMAX > 0) {
+    if (tid < p.T) topk_of_token<EMAX>(p.logits + (long)tid * E, E, p.topk, p.renormalize, p.topk_ids + (long)tid * p.topk, p.topk_w + (long)tid * p.topk);
+  }
+  s_cnt[wave][lane] = 0;   // kMaxExperts = 64 counters per wave
+  for (int i = tid; i < kLdsTiles; i += kRouteThreads) { s_mlo[i] = 0; s_mhi[i] = 0; }
+  __syncthreads();   // (step 1's expert indices too are where every wave of this workgroup sees them)
+  // the expert indices of kRouteAhead steps from `base` on; -1 beyond the wave's range
+  auto load_ids = [&](int base, int (&id)[kRouteAhead]) {
+#pragma unroll
+    for (int u = 0; u < kRouteAhead; u++) {
+      const int r = base + u * 64 + lane;
+      id[u] = r < hi ? p.topk_ids[r] : -1;
+    }
+  };
   // ---- pass A: rows per (wave, expert)
-  for (int base = lo; base < hi; base += 64) {
-    const int r = base + lane;
-    const bool valid = r < hi;
-    const int e = valid ? topk_ids[r] : 0;
-    const unsigned long long same = same_expert_lanes(e, valid);
-    if (valid && (same & below) == 0) s_cnt[wave][e] += __builtin_popcountll(same);  // the group's first lane
+  for (int base = lo; base < hi; base += 64 * kRouteAhead) {
+    int id[kRouteAhead];
+    load_ids(base, id);
+#pragma unroll
+    for (int u = 0; u < kRouteAhead; u++) {
+      if (base + u * 64 >= hi) break;
+      const bool valid = id[u] >= 0;
+      const unsigned long long same = same_expert_lanes(id[u], valid, E);
+      if (valid && (same & below) == 0) atomicAdd(&s_cnt[wave][id[u]], __builtin_popcountll(same));  // the group's first lane
+    }
   }
   __syncthreads();
   // ---- offsets, tile bases, start position of every (wave, expert)
-  if (tid < E) {
-    int tot = 0;
-    for (int w = 0; w < kRouteWaves; w++) tot += s_cnt[w][tid];
-    s_off[tid + 1] = tot;
+  if (wave == 0) {
+    int c[kRouteWaves], tot = 0;
+#pragma unroll
+    for (int w = 0; w < kRouteWaves; w++) { c[w] = s_cnt[w][lane]; tot += c[w]; }
+    const int tiles = (int)p.by_tile.div((unsigned)(tot + Tm - 1));
+    int off = tot, tb = tiles;   // inclusive scans over the experts
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+      const int o = __shfl_up(off, d), t = __shfl_up(tb, d);
+      if (lane >= d) { off += o; tb += t; }
+    }
+    if (lane == 0) { s_off[0] = 0; s_tbase[0] = 0; }
+    s_off[lane + 1] = off;
+    s_tbase[lane + 1] = tb;
+    if (lane == 63) *p.n_tiles = tb;   // experts from E on have no rows
+    int run = off - tot;
+#pragma unroll
+    for (int w = 0; w < kRouteWaves; w++) { s_cnt[w][lane] = run; run += c[w]; }
   }
   __syncthreads();
-  if (tid == 0) {
-    int run = 0, tb = 0;
-    for (int e = 0; e < E; e++) {
-      int c = s_off[e + 1];
-      s_off[e] = run;
-      s_tbase[e] = tb;
-      run += c;
-      tb += (c + Tm - 1) / Tm;
-    }
-    s_off[E] = run;
-    s_tbase[E] = tb;
-    *n_tiles = tb;
-  }
-  __syncthreads();
-  if (tid < E) {
-    int run = s_off[tid];
-    for (int w = 0; w < kRouteWaves; w++) {
-      int c = s_cnt[w][tid];
-      s_cnt[w][tid] = run;
-      run += c;
-    }
-  }
   const int nt = s_tbase[E];
   const bool in_lds = nt <= kLdsTiles;
-  // ---- tile records: range and expert now, masks and rank span start empty
-  for (int tau = tid; tau < nt; tau += kRouteThreads) {
-    int e = 0;
-    while (s_tbase[e + 1] <= tau) e++;
-    int f_lo = s_off[e] + (tau - s_tbase[e]) * Tm;
-    int* rec = tile_tables + (long)tau * 8;
-    rec[0] = f_lo; rec[1] = min(f_lo + Tm, s_off[e + 1]); rec[2] = e; rec[7] = 0;
-    if (in_lds) { s_mlo[tau] = 0; s_mhi[tau] = 0; s_rmin[tau] = R; s_rmax[tau] = -1; }
-    else { rec[3] = 0; rec[4] = 0; rec[5] = R; rec[6] = -1; }
+  if (!in_lds) {
+    for (int tau = tid; tau < nt; tau += kRouteThreads) {
+      int* rec = p.tile_tables + (long)tau * 8;
+      rec[3] = 0; rec[4] = 0;
+    }
+    __threadfence();
+    __syncthreads();
   }
-  __threadfence();
-  __syncthreads();
-  // ---- pass B: place the rows, collect each tile's channels and source ranks
-  const int tokens_per_rank = T / R, tokens_per_channel = tokens_per_rank / C;
-  for (int base = lo; base < hi; base += 64) {
-    const int r = base + lane;
-    const bool valid = r < hi;
-    const int e = valid ? topk_ids[r] : 0;
-    const unsigned long long same = same_expert_lanes(e, valid);
-    int start = 0;
-    if (valid) start = s_cnt[wave][e];
-    if (valid && (same & below) == 0) s_cnt[wave][e] = start + __builtin_popcountll(same);
-    if (valid) {
-      const int pos = start + __builtin_popcountll(same & below);
-      sorted_row[pos] = r;
-      const int tau = s_tbase[e] + (pos - s_off[e]) / Tm;
-      const int token = r / topk, ch = token / tokens_per_channel, q = token / tokens_per_rank;
-      if (in_lds) {
-        if (ch < 32) atomicOr(&s_mlo[tau], 1u << ch); else atomicOr(&s_mhi[tau], 1u << (ch - 32));
-        atomicMin(&s_rmin[tau], q);
-        atomicMax(&s_rmax[tau], q);
-      } else {
-        int* rec = tile_tables + (long)tau * 8;
-        if (ch < 32) atomicOr((unsigned*)rec + 3, 1u << ch); else atomicOr((unsigned*)rec + 4, 1u << (ch - 32));
-        atomicMin(rec + 5, q);
-        atomicMax(rec + 6, q);
+  // ---- pass B: place the rows, collect each tile's channels
+  for (int base = lo; base < hi; base += 64 * kRouteAhead) {
+    int id[kRouteAhead];
+    load_ids(base, id);
+#pragma unroll
+    for (int u = 0; u < kRouteAhead; u++) {
+      if (base + u * 64 >= hi) break;
+      const int r = base + u * 64 + lane, e = id[u];
+      const bool valid = e >= 0;
+      const unsigned long long same = same_expert_lanes(e, valid, E);
+      int start = 0;
+      if (valid) start = s_cnt[wave][e];
+      if (valid && (same & below) == 0) s_cnt[wave][e] = start + __builtin_popcountll(same);
+      if (valid) {
+        const int pos = start + __builtin_popcountll(same & below);
+        p.sorted_row[pos] = r;
+        const int tau = s_tbase[e] + (int)p.by_tile.div((unsigned)(pos - s_off[e]));
+        const int ch = (int)p.by_channel.div((unsigned)r);
+        if (in_lds) {
+          if (ch < 32) atomicOr(&s_mlo[tau], 1u << ch); else atomicOr(&s_mhi[tau], 1u << (ch - 32));
+        } else {
+          unsigned* rec = (unsigned*)p.tile_tables + (long)tau * 8;
+          if (ch < 32) atomicOr(rec + 3, 1u << ch); else atomicOr(rec + 4, 1u << (ch - 32));
+        }
       }
     }
   }
+  if (!in_lds) __threadfence();
   __syncthreads();
-  for (int e = tid; e <= E; e += kRouteThreads) expert_offsets[e] = s_off[e];
-  if (in_lds)
-    for (int tau = tid; tau < nt; tau += kRouteThreads) {
-      int* rec = tile_tables + (long)tau * 8;
-      rec[3] = (int)s_mlo[tau]; rec[4] = (int)s_mhi[tau]; rec[5] = s_rmin[tau]; rec[6] = s_rmax[tau];
+  for (int e = tid; e <= E; e += kRouteThreads) p.expert_offsets[e] = s_off[e];
+  // ---- tile records: (f_S_low, f_S_high, expert, channel mask, first and last source rank, 0)
+  for (int tau = tid; tau < nt; tau += kRouteThreads) {
+    int e = 0;   // the last expert whose tiles start at or before tau (one without tiles starts where the next one does)
+#pragma unroll
+    for (int d = 32; d >= 1; d /= 2)
+      if (e + d < E && s_tbase[e + d] <= tau) e += d;
+    int* rec = p.tile_tables + (long)tau * 8;
+    const int f_lo = s_off[e] + (tau - s_tbase[e]) * Tm;
+    unsigned mlo, mhi;
+    if (in_lds) { mlo = s_mlo[tau]; mhi = s_mhi[tau]; }
+    else {
+      mlo = __hip_atomic_load((unsigned*)rec + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      mhi = __hip_atomic_load((unsigned*)rec + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    const unsigned long long mask = (unsigned long long)mlo | ((unsigned long long)mhi << 32);   // a tile has rows: not empty
+    rec[0] = f_lo; rec[1] = min(f_lo + Tm, s_off[e + 1]); rec[2] = e;
+    rec[3] = (int)mlo; rec[4] = (int)mhi;
+    rec[5] = __builtin_ctzll(mask) / p.C; rec[6] = (63 - __builtin_clzll(mask)) / p.C; rec[7] = 0;
+  }
 }
 
 // ======================================================================================
@@ -623,10 +704,26 @@ int tl_moe_route(tl_ctx* ctx, const float* gate_logits, int T, int E, int topk, 
   if (T % c.world_size || (T / c.world_size) % c.channels_per_rank) return fail(TL_ERR_UNSUPPORTED_SHAPE, "tl_moe_route: R must divide T and C must divide T/R");
   if (c.world_size * c.channels_per_rank > 64) return fail(TL_ERR_UNSUPPORTED_SHAPE, "tl_moe_route: at most 64 AllGather channels");
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(moe_topk_kernel, dim3((T + 255) / 256), dim3(256), 0, s, gate_logits, T, E, topk, renormalize, topk_ids, topk_w);
-  TL_HIP(hipGetLastError());
-  hipLaunchKernelGGL(moe_sort_kernel, dim3(1), dim3(kRouteThreads), 0, s, topk_ids, T * topk, E, topk, T, c.world_size, c.channels_per_rank,
-                     tile_m, expert_offsets, sorted_row, tile_tables, n_tiles);
+  RouteParams p;
+  memset(&p, 0, sizeof p);
+  p.logits = gate_logits; p.topk_ids = topk_ids; p.topk_w = topk_w;
+  p.n_rows = T * topk; p.E = E; p.topk = topk; p.T = T; p.renormalize = renormalize;
+  p.C = c.channels_per_rank; p.Tm = tile_m;
+  p.by_channel = make_fast_div((unsigned)(T / c.world_size / c.channels_per_rank) * (unsigned)topk);
+  p.by_tile = make_fast_div((unsigned)tile_m);
+  p.expert_offsets = expert_offsets; p.sorted_row = sorted_row; p.tile_tables = tile_tables; p.n_tiles = n_tiles;
+  // up to kRouteThreads tokens both steps are one launch (a thread per token); beyond that step 1 wants the whole chip
+  const bool one = T <= kRouteThreads;
+  auto go = [&](auto emax_c) {
+    constexpr int EMAX = decltype(emax_c)::value;
+    if (one) { hipLaunchKernelGGL(moe_sort_kernel<EMAX>, dim3(1), dim3(kRouteThreads), 0, s, p); return; }
+    hipLaunchKernelGGL(moe_topk_kernel<EMAX>, dim3((T + 63) / 64), dim3(64), 0, s, gate_logits, T, E, topk, renormalize, topk_ids, topk_w);
+    hipLaunchKernelGGL(moe_sort_kernel<0>, dim3(1), dim3(kRouteThreads), 0, s, p);
+  };
+  if (E <= 8) go(std::integral_constant<int, 8>{});
+  else if (E <= 16) go(std::integral_constant<int, 16>{});
+  else if (E <= 32) go(std::integral_constant<int, 32>{});
+  else go(std::integral_constant<int, 64>{});
   TL_HIP(hipGetLastError());
   return TL_OK;
 }
