@@ -52,7 +52,9 @@ __device__ __forceinline__ void both_halves(float v, float& lo, float& hi) {
 // v_max_f32 on the raw registers; fmaxf() on them would first canonicalise each operand with an instruction of its own.
 __device__ __forceinline__ float raw_max(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, __builtin_inff()); }
 
-// max(m, a, b) in one instruction on raw matrix-instruction results (finite or -inf)
+// max(m, a, b) in one instruction on raw matrix-instruction results (finite or -inf).  The compiler does not look into it
+// and keeps no distance from the matrix instruction that writes a or b: only where at least two later matrix instructions
+// stand in between and cover that one's latency; raw_max() elsewhere.
 __device__ __forceinline__ float raw_max3(float m, float a, float b) {
   float r;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(a), "v"(b));
@@ -206,7 +208,7 @@ __global__ void __launch_bounds__(512 / QT) sp_attention_kernel(const AttnParams
   auto block_max = [&](const floatx16 (&sc)[2]) __attribute__((always_inline)) -> float {
     float m = -1e30f;
 #pragma unroll
-    for (int e = 0; e < 16; e++) m = raw_max3(m, sc[0][e], sc[1][e]);
+    for (int e = 0; e < 16; e++) m = raw_max(raw_max(m, sc[0][e]), sc[1][e]);
     return halves_max(m);
   };
   float m_blk[QT];   // block_max of the block the next iteration works on, computed one iteration early
