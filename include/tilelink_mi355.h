@@ -189,7 +189,8 @@ int tl_read_clocks(tl_ctx* ctx, void* workspace /*dev*/, long long* out /*host, 
  *              producer workgroups and to GEMM workgroups that would otherwise wait -- or, where the launch is one round of
  *              workgroups, split over all of them by index.  Where several workgroups share a tile along K the query asks
  *              for more than 256 bytes (counters and fp32 partial tiles behind the first 256); with 256 bytes the same call
- *              computes whole tiles (the sums then differ in their last bits).
+ *              computes whole tiles (the sums then differ in their last bits).  The counters are zero again after every
+ *              call, so what lies behind the first 256 bytes is zeroed once, in every comm_mode, and never again.
  *   compute_stream receives the fused kernel; comm_stream the copies in TL_COMM_STREAM and COPY_ENGINE mode.  In SIDE_KERNEL
  *   mode the producers join the GEMM's launch (GEMM workgroups copy there in any case, so nothing of the gather can be relied
  *   on in comm_stream's order alone); a kernel of their own on comm_stream they are with comm_workgroups, link_gbps or

@@ -26,7 +26,7 @@ struct AgGemmParams {
   int splits;           // > 1: this many workgroups share every tile, each with split_steps of its K steps (one position per workgroup)
   int split_steps;
   float* slots;         // [n_tiles][splits] slots of BM x BN floats
-  unsigned* counts;     // [n_tiles] workgroups that have left their part; each grows by `splits` per call
+  unsigned* counts;     // [n_tiles] workgroups that have left their part; zero between calls
 };
 
 struct GemmRsParams {
@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(Cfg::NTHREADS) ag_gemm_kernel(const AgGemmPara
       const int k_lo = part * p.split_steps * Cfg::BK, k_n = min(p.K - k_lo, p.split_steps * Cfg::BK);
       gemm_tile<Cfg>(p.prod.gathered + (long)row_lo * p.K + k_lo, p.K, nullptr, 1, p.b + (long)k_lo * p.N + col_lo, p.N, out, rows, cols, k_n, smem,
                      NoKWait{}, NoHook{},
-                     SplitK<Cfg>{p.slots + (long)tile * p.splits * SplitK<Cfg>::SLOT, p.counts + tile, p.prod.epoch * (unsigned)p.splits - 1u, p.splits, part, &s_ticket});
+                     SplitK<Cfg>{p.slots + (long)tile * p.splits * SplitK<Cfg>::SLOT, p.counts + tile, p.splits, part, &s_ticket});
     } else if (p.prod.k_chunks > 1 && p.do_wait) {
       gemm_tile<Cfg>(p.prod.gathered + (long)row_lo * p.K, p.K, nullptr, 1, p.b + col_lo, p.N, out, rows, cols, p.K, smem,
                      ChunkWait{p.prod.flags, p.prod.k_chunks, p.K / Cfg::BK / p.prod.k_chunks, clo, chi, p.prod.wait_target, p.prod.ctl});
@@ -419,10 +419,12 @@ static int choose_splits(long tiles, int K, int cus, double* us) {
   return best;
 }
 
-// Scratch of a call whose tiles are shared (after the first 256 bytes of the workspace): counters, then slots.
-static size_t split_count_bytes(const Resolved& r) { return ((size_t)r.n_tiles * sizeof(unsigned) + 255) / 256 * 256; }
-static size_t split_bytes(const Resolved& r) {
-  return r.splits > 1 ? split_count_bytes(r) + (size_t)r.n_tiles * r.splits * r.tile_m * r.tile_n * sizeof(float) : 0;
+// Scratch of a call whose tiles are shared (after the first 256 bytes of the workspace): counters, then slots.  The
+// counters have room for the most tiles that can be shared -- two workgroups each -- whatever the shape: calls of several
+// shapes may follow one another on one workspace, and no slot of the one may lie where the other keeps a counter.
+static size_t split_count_bytes(const tl_ctx* ctx) { return ((size_t)(ctx->num_cus / 2) * sizeof(unsigned) + 255) / 256 * 256; }
+static size_t split_bytes(const tl_ctx* ctx, const Resolved& r) {
+  return r.splits > 1 ? split_count_bytes(ctx) + (size_t)r.n_tiles * r.splits * r.tile_m * r.tile_n * sizeof(float) : 0;
 }
 
 int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, bool paired_columns) {
@@ -692,9 +694,9 @@ int tl_query_workspace(const tl_ctx* ctx, int op, const long long* dims, size_t*
     *ws_bytes = 256;  // status word (+ padding)
     if (op == TL_OP_AG_GEMM) {
       *n_flags = (size_t)ctx->cfg.world_size * ctx->cfg.channels_per_rank * r.k_chunks;
-      size_t scratch = split_bytes(r);
+      size_t scratch = split_bytes(ctx, r);
       Resolved g;   // the gated form may choose another tile
-      if (dims[1] % 64 == 0 && resolve_dense(ctx, op, (int)dims[0], (int)dims[1], (int)dims[2], &g, true) == TL_OK && split_bytes(g) > scratch) scratch = split_bytes(g);
+      if (dims[1] % 64 == 0 && resolve_dense(ctx, op, (int)dims[0], (int)dims[1], (int)dims[2], &g, true) == TL_OK && split_bytes(ctx, g) > scratch) scratch = split_bytes(ctx, g);
       *ws_bytes += scratch;
     } else {
       size_t tiles_per_seg = (size_t)(r.rows_per_rank / r.Tm_p) * r.n_ptn;
@@ -818,12 +820,12 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
   p.sched = make_sched(ctx, r, TL_OP_AG_GEMM);
   int G = r.G;
   p.splits = 1;
-  if (r.splits > 1 && ws_bytes >= 256 + split_bytes(r)) {   // (a smaller workspace, as the static entry point's: whole tiles)
+  if (r.splits > 1 && ws_bytes >= 256 + split_bytes(ctx, r)) {   // (a smaller workspace, as the static entry point's: whole tiles)
     const int steps = ceil_div(K, Cfg128x128::BK);
     p.splits = r.splits;
     p.split_steps = ceil_div(steps, r.splits);
     p.counts = (unsigned*)((char*)workspace + 256);
-    p.slots = (float*)((char*)workspace + 256 + split_count_bytes(r));
+    p.slots = (float*)((char*)workspace + 256 + split_count_bytes(ctx));
     p.sched.n_tiles *= r.splits;
     p.sched.G *= r.splits;
     G *= r.splits;

@@ -130,14 +130,15 @@ struct NoSplit {
 // leaves its fp32 accumulators in its slot of the tile's scratch, in accumulator order (a lane's 16-byte pieces, so every
 // store covers 1 KiB), written through to device scope, and counts itself in; the one that finds all others counted
 // adds the slots in the order s = 0, 1, .. (its own from registers: the sum does not depend on who comes last) and goes
-// on to the epilogue.  Nobody waits for anybody.  The slots' lines are read by no one before the count says they are
-// complete, so the fence after the count leaves the caches alone (see TL_ACQ_SCOPE).
+// on to the epilogue.  Nobody waits for anybody.  The last one takes the count back to zero: every workgroup of a call
+// counts itself in, also after a wait that expired, so each call finds zero whatever its epoch is and whatever call came
+// before it.  The slots' lines are read by no one before the count says they are complete, so the fence after the count
+// leaves the caches alone (see TL_ACQ_SCOPE).
 template <class Cfg>
 struct SplitK {
   static constexpr bool ENABLED = true;
   float* slots;        // the tile's S slots of BM x BN floats
-  unsigned* count;     // grows by S per call
-  unsigned last;       // its value (before the add) that the last workgroup of this call finds
+  unsigned* count;     // workgroups that have left their part; zero between calls
   int S, s;
   int* s_old;          // an int in LDS
   static constexpr int SLOT = Cfg::BM * Cfg::BN;
@@ -158,7 +159,8 @@ struct SplitK {
     __syncthreads();   // every wave's part of the slot is where every die sees it
     if (wave == 0) *s_old = (int)lane0_fetch_add(count, 1u);
     __syncthreads();
-    if ((unsigned)__builtin_amdgcn_readfirstlane(*s_old) != last) return false;
+    if (__builtin_amdgcn_readfirstlane(*s_old) != S - 1) return false;
+    if (wave == 0) lane0_add(count, 0u - (unsigned)S);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, TL_ACQ_SCOPE);
     floatx16 sum[Cfg::MT][Cfg::NT];
 #pragma unroll

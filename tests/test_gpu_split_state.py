@@ -1,0 +1,101 @@
+"""AllGather + GEMM tiles that several workgroups share along K, where calls repeat or follow one another on one workspace
+in other ways than a growing epoch of one call: no part of the result may depend on what an earlier call left there."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2503_20313_amd as tl
+import tl_workloads as wl
+from oracle import ops
+from tests.gpu_util import assert_close_bf16, dev, down, make_ctx, poison, up
+from tests.test_gpu_ag_gemm import check, run_ag_gemm
+
+pytestmark = pytest.mark.gpu
+
+
+class Call:
+    """Buffers of one AllGather + GEMM shape; the workspace may be another call's."""
+
+    def __init__(self, M, N, K, R, config_id, gathered=False):
+        self.dims, self.R = (M, N, K), R
+        self.w = wl.ag_gemm_inputs(M, N, K, R, config_id=config_id)
+        self.shards = [up(s) for s in self.w["a_shards"]]
+        self.gathered = up(np.concatenate(self.w["a_shards"])) if gathered else poison((M, K))
+        self.b, self.c = up(self.w["b"]), poison((M, N))
+        self.ref = ops.ag_gemm(self.w["a_shards"], self.w["b"])[2]
+
+    def run(self, ctx, flags, epoch, ws, ws_bytes):
+        self.c.copy_(poison(self.c.shape))
+        torch.cuda.synchronize()
+        tl.tl_ag_gemm(ctx, self.shards, self.gathered, self.b, self.c, *self.dims, flags, epoch, ws, ws_bytes)
+        torch.cuda.synchronize()
+
+    def check(self, what):
+        assert_close_bf16(down(self.c), self.ref, what)
+
+
+def scratch(ctx, *calls):
+    """A zeroed workspace for the largest of the calls, and flags."""
+    q = [tl.tl_query_workspace(ctx, tl.TL_OP_AG_GEMM, list(c.dims)) for c in calls]
+    assert all(b > 256 for b, _ in q), "these calls are meant to share tiles along K"
+    ws_bytes, n_flags = max(b for b, _ in q), max(f for _, f in q)
+    return torch.zeros(ws_bytes // 4, dtype=torch.int32, device=dev()), ws_bytes, torch.zeros(n_flags, dtype=torch.int32, device=dev())
+
+
+@pytest.mark.parametrize("epochs", [(1, 1, 1), (7, 7, 3)])
+def test_without_communication_the_epoch_has_no_meaning(epochs):
+    ctx = make_ctx(world_size=2, rank=0, comm_mode=tl.TL_COMM_NONE)
+    call = Call(256, 264, 4096, 2, 171, gathered=True)
+    ws, ws_bytes, flags = scratch(ctx, call)
+    for i, epoch in enumerate(epochs):
+        call.run(ctx, flags, epoch, ws, ws_bytes)
+        call.check(f"call {i}, epoch {epoch}")
+    tl.tl_ctx_destroy(ctx)
+
+
+def test_two_shapes_on_one_workspace():
+    """72 tiles and 2 tiles in turn: the counters of the one are not where the partial sums of the other go."""
+    ctx = make_ctx(world_size=2, rank=0, comm_mode=tl.TL_COMM_NONE)
+    calls = [Call(1024, 1152, 3072, 2, 172, gathered=True), Call(128, 200, 8192, 2, 173, gathered=True)]
+    ws, ws_bytes, flags = scratch(ctx, *calls)
+    for i in range(4):
+        calls[i % 2].run(ctx, flags, i + 1, ws, ws_bytes)
+        calls[i % 2].check(f"call {i}")
+    tl.tl_ctx_destroy(ctx)
+
+
+def test_retry_after_a_withheld_flag():
+    ctx = make_ctx(world_size=2, rank=0, comm_mode=tl.TL_COMM_EXTERNAL, spin_timeout_us=20_000)
+    call = Call(256, 128, 4096, 2, 174, gathered=True)
+    ws, ws_bytes, flags = scratch(ctx, call)
+    expected = tl.tl_resolve(ctx, tl.TL_OP_AG_GEMM, list(call.dims))["expected_per_channel"]
+    flags[0] = expected
+    call.run(ctx, flags, 1, ws, ws_bytes)
+    with pytest.raises(tl.TileLinkError) as e:
+        tl.tl_check_status(ctx, ws)
+    assert e.value.status == tl.TL_ERR_TIMEOUT
+    flags[1] = expected
+    call.run(ctx, flags, 1, ws, ws_bytes)      # the same call again, now complete
+    tl.tl_check_status(ctx, ws)
+    call.check("retry")
+    tl.tl_ctx_destroy(ctx)
+
+
+def test_communication_alone_between_two_calls():
+    cfg = dict(world_size=2, rank=1, comm_mode=tl.TL_COMM_SIDE_KERNEL)
+    ctx, alone = make_ctx(**cfg), make_ctx(comm_alone=1, **cfg)
+    call = Call(256, 264, 4096, 2, 175)
+    ws, ws_bytes, flags = scratch(ctx, call)
+    for epoch, c in ((1, ctx), (2, alone), (3, ctx)):
+        call.run(c, flags, epoch, ws, ws_bytes)
+        tl.tl_check_status(c, ws)
+        if c is ctx:
+            call.check(f"epoch {epoch}")
+    for c in (ctx, alone):
+        tl.tl_ctx_destroy(c)
+
+
+def test_shared_tiles_behind_the_copy_engine():
+    w = wl.ag_gemm_inputs(256, 264, 4104, 2, config_id=176)
+    hs, g, c, flags, info = run_ag_gemm(w, 1, 2, tl.TL_COMM_COPY_ENGINE, epochs=3)
+    check(w, hs, g, c, "copy engine")
