@@ -421,11 +421,17 @@ static int choose_splits(long tiles, int K, int cus, double* us) {
 
 // Scratch of a call whose tiles are shared (after the first 256 bytes of the workspace): counters, then slots.  The
 // counters have room for the most tiles that can be shared -- two workgroups each -- whatever the shape: calls of several
-// shapes may follow one another on one workspace, and no slot of the one may lie where the other keeps a counter.
+// shapes may follow one another on one workspace, and no slot of the one may lie where the other keeps a counter.  The
+// slots start on a cache line, wherever the workspace does: the fence that combine() takes leaves the caches alone, so a
+// line that held the end of one tile's slots and the start of the next one's could be read stale (see TL_ACQ_SCOPE).
 static size_t split_count_bytes(const tl_ctx* ctx) { return ((size_t)(ctx->num_cus / 2) * sizeof(unsigned) + 255) / 256 * 256; }
-static size_t split_bytes(const tl_ctx* ctx, const Resolved& r) {
-  return r.splits > 1 ? split_count_bytes(ctx) + (size_t)r.n_tiles * r.splits * r.tile_m * r.tile_n * sizeof(float) : 0;
+static size_t split_slot_offset(const tl_ctx* ctx, const void* workspace) {
+  const size_t at = 256 + split_count_bytes(ctx);
+  return at + (128 - ((uintptr_t)workspace + at) % 128) % 128;
 }
+static size_t split_slot_bytes(const Resolved& r) { return r.splits > 1 ? (size_t)r.n_tiles * r.splits * r.tile_m * r.tile_n * sizeof(float) : 0; }
+// What the query asks for behind the first 256 bytes: it does not know where the workspace will lie.
+static size_t split_bytes(const tl_ctx* ctx, const Resolved& r) { return r.splits > 1 ? split_count_bytes(ctx) + 128 + split_slot_bytes(r) : 0; }
 
 int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, bool paired_columns) {
   const tl_config& c = ctx->cfg;
@@ -820,12 +826,13 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
   p.sched = make_sched(ctx, r, TL_OP_AG_GEMM);
   int G = r.G;
   p.splits = 1;
-  if (r.splits > 1 && ws_bytes >= 256 + split_bytes(ctx, r)) {   // (a smaller workspace, as the static entry point's: whole tiles)
+  const size_t slots_at = split_slot_offset(ctx, workspace);
+  if (r.splits > 1 && ws_bytes >= slots_at + split_slot_bytes(r)) {   // (a smaller workspace, as the static entry point's: whole tiles)
     const int steps = ceil_div(K, Cfg128x128::BK);
     p.splits = r.splits;
     p.split_steps = ceil_div(steps, r.splits);
     p.counts = (unsigned*)((char*)workspace + 256);
-    p.slots = (float*)((char*)workspace + 256 + split_count_bytes(ctx));
+    p.slots = (float*)((char*)workspace + slots_at);
     p.sched.n_tiles *= r.splits;
     p.sched.G *= r.splits;
     G *= r.splits;

@@ -99,3 +99,25 @@ def test_shared_tiles_behind_the_copy_engine():
     w = wl.ag_gemm_inputs(256, 264, 4104, 2, config_id=176)
     hs, g, c, flags, info = run_ag_gemm(w, 1, 2, tl.TL_COMM_COPY_ENGINE, epochs=3)
     check(w, hs, g, c, "copy engine")
+
+
+@pytest.mark.parametrize("offset", [0, 32, 96])
+def test_partial_sums_start_on_a_cache_line(offset):
+    """A workspace that starts in the middle of a cache line: no line may hold partial sums of two tiles, and what the
+    query asked for is enough.  Words in front of the partial sums are zero after the call, so the first one that is not
+    tells where they start."""
+    ctx = make_ctx(world_size=2, rank=0, comm_mode=tl.TL_COMM_NONE)
+    call = Call(256, 264, 4096, 2, 177, gathered=True)
+    ws_bytes, n_flags = tl.tl_query_workspace(ctx, tl.TL_OP_AG_GEMM, list(call.dims))
+    guard = 64
+    buf = torch.zeros(offset // 4 + ws_bytes // 4 + guard, dtype=torch.int32, device=dev())
+    assert buf.data_ptr() % 128 == 0
+    ws, flags = buf[offset // 4:], torch.zeros(n_flags, dtype=torch.int32, device=dev())
+    for epoch in (1, 2):
+        call.run(ctx, flags, epoch, ws, ws_bytes)
+        call.check(f"workspace at {offset}, epoch {epoch}")
+    words = buf.cpu().numpy()
+    first = int(np.flatnonzero(words[(offset + 256) // 4:])[0]) + (offset + 256) // 4
+    assert first * 4 % 128 < 16, first * 4            # (the first of N(0, 1) sums may itself be a zero)
+    assert not words[(offset + ws_bytes) // 4:].any()
+    tl.tl_ctx_destroy(ctx)
