@@ -547,14 +547,15 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     // workgroups in front of the GEMM's -- on compute units its only round leaves free if there are some --, no more than
     // there are tiles to copy for two each (the waiting GEMM workgroups copy too, and every one that asks in vain holds up
     // the queue).  As a kernel of their own they start 6 us behind the GEMM, which waits for them: measured, fused,
-    // [8192,8192] x [8192,3584] 440 -> 420 us, [8192,4096] x [4096,1376] 128 -> 120 us.
+    // [8192,8192] x [8192,3584] 440 -> 420 us, [8192,4096] x [4096,1376] 128 -> 120 us.  With comm_alone there is no GEMM
+    // workgroup that could copy: the side kernel as it is without a GEMM, or the 64.
     r->fold = 0;
-    if (c.comm_workgroups == 0 && c.link_gbps == 0 && (c.comm_mode == TL_COMM_WAVES || c.comm_mode == TL_COMM_SIDE_KERNEL)) {
+    if (c.comm_workgroups == 0 && c.link_gbps == 0 && (c.comm_mode == TL_COMM_WAVES || (c.comm_mode == TL_COMM_SIDE_KERNEL && !c.comm_alone))) {
       r->fold = 1;
       const int idle = (ctx->num_cus - G * r->splits) / kXcds * kXcds, work = ceil_div(r->n_ptm * r->n_ptn, 2 * kXcds) * kXcds;
-      const int n = idle >= 16 && idle < 64 ? idle : 64;
+      const int n = idle >= 16 && idle < 64 && !c.comm_alone ? idle : 64;
       r->n_comm = n < work ? n : work;
-      if (r->k_chunks == 1 && r->n_tiles * r->splits <= ctx->num_cus) r->n_comm = idle < work ? idle : work;   // shares: as many as there is room for
+      if (r->k_chunks == 1 && r->n_tiles * r->splits <= ctx->num_cus && !c.comm_alone) r->n_comm = idle < work ? idle : work;   // shares: as many as there is room for
     }
     r->first_block = 0;
     if (c.tile_order != TL_ORDER_NATURAL) {
@@ -841,7 +842,7 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
 
   const bool alone = cfg.comm_alone != 0;  // communication side only (timing)
   // shares: the whole launch has to fit on the chip at once (and nothing but the gather itself is to be done)
-  const bool share = r.fold && !peer_slots && G + r.n_comm <= ctx->num_cus && (r.k_chunks == 1 || r.n_comm >= 16);
+  const bool share = r.fold && !alone && !peer_slots && G + r.n_comm <= ctx->num_cus && (r.k_chunks == 1 || r.n_comm >= 16);
   if (r.k_chunks > 1 && cfg.comm_mode != TL_COMM_WAVES && cfg.comm_mode != TL_COMM_SIDE_KERNEL) r.k_chunks = 1;
   if (alone && (cfg.comm_mode == TL_COMM_NONE || cfg.comm_mode == TL_COMM_EXTERNAL))
     return fail(TL_ERR_INVALID_ARG, "tl_ag_gemm: comm_alone needs a comm_mode in which the library runs a producer");
@@ -853,14 +854,14 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
     case TL_COMM_WAVES:
       p.n_comm = r.n_comm; p.do_wait = 1;
       p.prod.wait_target = epoch * (unsigned)r.expected;
-      p.share = share && !alone;
+      p.share = share;
       return launch_ag_gemm(r.variant, p, alone ? r.n_comm : G + r.n_comm, cs);
     case TL_COMM_EXTERNAL:
       p.n_comm = 0; p.do_wait = 2;
       p.prod.wait_target = epoch * (unsigned)r.expected;
       return launch_ag_gemm(r.variant, p, G, cs);
     case TL_COMM_SIDE_KERNEL: {
-      if (r.fold && !alone) {   // (on ms alone nothing of the gather may be relied on in this binding either way: GEMM workgroups copy too)
+      if (r.fold) {   // (on ms alone nothing of the gather may be relied on in this binding either way: GEMM workgroups copy too)
         p.n_comm = r.n_comm; p.do_wait = 1;
         p.prod.wait_target = epoch * (unsigned)r.expected;
         p.share = share;
@@ -870,7 +871,7 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
       // hardware queue the worst case is that the two kernels run one after the other.
       p.n_comm = 0; p.do_wait = 1;
       p.prod.wait_target = epoch * (unsigned)r.expected;
-      hipLaunchKernelGGL(ag_producer_kernel, dim3(r.fold ? 128 : r.n_comm), dim3(256), 0, ms, p.prod);
+      hipLaunchKernelGGL(ag_producer_kernel, dim3(r.n_comm), dim3(256), 0, ms, p.prod);
       TL_HIP(hipGetLastError());
       return alone ? TL_OK : launch_ag_gemm(r.variant, p, G, cs);
     }

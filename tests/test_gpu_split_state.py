@@ -121,3 +121,20 @@ def test_partial_sums_start_on_a_cache_line(offset):
     assert first * 4 % 128 < 16, first * 4            # (the first of N(0, 1) sums may itself be a zero)
     assert not words[(offset + ws_bytes) // 4:].any()
     tl.tl_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("mode", [tl.TL_COMM_WAVES, tl.TL_COMM_SIDE_KERNEL])
+@pytest.mark.parametrize("M,N,K", [(1024, 1024, 2048), (2048, 2048, 512)])     # shared tiles / whole tiles that fill the chip
+def test_communication_alone_gathers(mode, M, N, K):
+    ctx = make_ctx(world_size=8, rank=3, channels_per_rank=2, comm_mode=mode, comm_alone=1)
+    call = Call(M, N, K, 8, 178)
+    ws_bytes, n_flags = tl.tl_query_workspace(ctx, tl.TL_OP_AG_GEMM, [M, N, K])
+    expected = tl.tl_resolve(ctx, tl.TL_OP_AG_GEMM, [M, N, K])["expected_per_channel"]
+    ws, flags = torch.zeros(ws_bytes // 4, dtype=torch.int32, device=dev()), torch.zeros(n_flags, dtype=torch.int32, device=dev())
+    for epoch in (1, 2):
+        call.gathered.copy_(poison((M, K)))
+        call.run(ctx, flags, epoch, ws, ws_bytes)
+        tl.tl_check_status(ctx, ws)
+        assert np.array_equal(down(call.gathered), np.concatenate(call.w["a_shards"]))
+        assert flags.tolist() == [epoch * expected] * 16
+    tl.tl_ctx_destroy(ctx)

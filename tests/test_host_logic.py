@@ -162,3 +162,12 @@ def test_schedules_match_the_mapping_oracle_on_seeded_random_shapes():
             checked += 1
         tl.tl_ctx_destroy(ctx)
     assert checked >= 150
+
+
+@pytest.mark.parametrize("mode", [tl.TL_COMM_WAVES, tl.TL_COMM_SIDE_KERNEL])
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 4096), (2048, 2048, 8192), (1024, 1024, 4096), (512, 3584, 8192), (256, 512, 512)])
+def test_communication_alone_has_workgroups(mode, M, N, K):
+    """Also where the tiles of the GEMM, which does not run, would fill the chip."""
+    ctx = host_ctx(world_size=8, comm_mode=mode, comm_alone=1)
+    assert tl.tl_resolve(ctx, tl.TL_OP_AG_GEMM, [M, N, K])["comm_workgroups"] >= 8
+    tl.tl_ctx_destroy(ctx)
