@@ -187,7 +187,7 @@ int tl_read_clocks(tl_ctx* ctx, void* workspace /*dev*/, long long* out /*host, 
  *              restarts at 1).  Bytes 16..23 hold the start time of the call in flight when link_gbps is set.  One call at
  *              a time per workspace.  In WAVES and SIDE_KERNEL mode producer tiles are handed out through this queue to the
  *              producer workgroups and to GEMM workgroups that would otherwise wait -- or, where the launch is one round of
- *              workgroups, split over all of them by index.  Where several workgroups share a tile along K the query asks
+ *              workgroups, split over all of them by index (word 1 grows by the same number).  Where several workgroups share a tile along K the query asks
  *              for more than 256 bytes (counters and fp32 partial tiles behind the first 256); with 256 bytes the same call
  *              computes whole tiles (the sums then differ in their last bits).  The counters are zero again after every
  *              call, so what lies behind the first 256 bytes is zeroed once, in every comm_mode, and never again.

@@ -63,6 +63,9 @@ __global__ void __launch_bounds__(Cfg::NTHREADS) ag_gemm_kernel(const AgGemmPara
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int s_ticket, s_share[3];
   const int tid = threadIdx.x;
+  // a gather by shares hands out nothing, but the queue moves on by a call's tickets all the same: the next call on this
+  // workspace may be one that uses it
+  if (p.share && blockIdx.x == 0 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0) lane0_add(p.prod.ticket, (unsigned)(p.prod.n_ptm * p.prod.n_ptn));
   if ((int)blockIdx.x < p.n_comm) {
     if (p.share) {
       // with K chunks the first one is everybody's, the others are copied beside the matrix work

@@ -138,3 +138,30 @@ def test_communication_alone_gathers(mode, M, N, K):
         assert np.array_equal(down(call.gathered), np.concatenate(call.w["a_shards"]))
         assert flags.tolist() == [epoch * expected] * 16
     tl.tl_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("mode", [tl.TL_COMM_WAVES, tl.TL_COMM_SIDE_KERNEL])
+def test_gather_by_shares_and_by_the_queue_in_turn(mode):
+    """Contexts of one shape on one workspace with a growing epoch: whoever comes next finds the queue where it expects it."""
+    M, N, K, R = 512, 264, 1024, 4
+    cfg = dict(world_size=R, rank=1, channels_per_rank=2, comm_mode=mode, spin_timeout_us=100_000)
+    ctxs = dict(shares=make_ctx(**cfg), queue=make_ctx(comm_workgroups=8, **cfg), alone=make_ctx(comm_alone=1, **cfg))
+    geometry = [tl.tl_resolve(c, tl.TL_OP_AG_GEMM, [M, N, K]) for c in ctxs.values()]
+    assert len({(g["comm_tile_m"], g["comm_tile_n"], g["expected_per_channel"]) for g in geometry}) == 1
+    call = Call(M, N, K, R, 179)
+    ws_bytes, n_flags = tl.tl_query_workspace(ctxs["shares"], tl.TL_OP_AG_GEMM, [M, N, K])
+    ws, flags = torch.zeros(ws_bytes // 4, dtype=torch.int32, device=dev()), torch.zeros(n_flags, dtype=torch.int32, device=dev())
+    for epoch, name in enumerate(["shares", "queue", "shares", "alone", "queue", "shares"], 1):
+        shards = [wl.normal_bf16((M // R, K), 1.0, 180, epoch, q) for q in range(R)]
+        for q in range(R):
+            call.shards[q].copy_(up(shards[q]))
+        call.ref = ops.ag_gemm(shards, call.w["b"])[2]
+        call.run(ctxs[name], flags, epoch, ws, ws_bytes)
+        tl.tl_check_status(ctxs[name], ws)
+        assert np.array_equal(down(call.gathered), np.concatenate(shards)), (epoch, name)
+        if name != "alone":
+            call.check(f"epoch {epoch}, {name}")
+        assert flags.tolist() == [epoch * geometry[0]["expected_per_channel"]] * (R * 2)
+        assert int(ws[1]) == epoch * geometry[0]["n_comm_tiles"]
+    for c in ctxs.values():
+        tl.tl_ctx_destroy(c)
