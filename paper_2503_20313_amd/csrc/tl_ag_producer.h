@@ -29,6 +29,7 @@ struct AgProducer {
   unsigned wait_target;             // epoch * expected
   unsigned* flags;                  // [R*C*k_chunks]
   unsigned* ticket;                 // producer-tile queue head (grows by n_ptm*n_ptn per call)
+  unsigned share_patience;          // gather by shares: ticks of the 100 MHz clock before a consumer fetches its rows itself
   unsigned ticket_end;              // epoch * number of tickets per call (producer tiles + pushes)
   int n_out;                        // push mode: tickets n_ptm*n_ptn .. +n_out-1 each push one producer tile of the LOCAL shard
                                     // into one peer's copy of the gathered matrix (tile_push_data) and notify that peer
@@ -159,10 +160,13 @@ __device__ __forceinline__ void gather_share(const AgProducer& p, int lo, int hi
   }
 }
 
-// consumer_tile_wait on a gather by shares: all channels' flags in one look (lane c polls channel c).  After kShareGrace
-// ticks without them the workgroup copies the missing rows itself -- the same bytes, so it does not matter that their owner
-// copies and notifies them as well once it runs -- and goes on.
-constexpr unsigned long long kShareGrace = 20000;   // 200 us on the 100 MHz clock
+// consumer_tile_wait on a gather by shares: all channels' flags in one look (lane c polls channel c).  After
+// p.share_patience ticks without them the workgroup copies the missing rows itself -- the same bytes, so it does not matter
+// that their owner copies and notifies them as well once it runs -- and goes on.  The patience covers the gather itself, or
+// all workgroups of a long one would start over with it together ([65536,8192] at 8 ranks: 1 GiB, 4.7 ms instead of 0.8);
+// and before each piece the channel is looked at again, for owners that were merely late.  With K chunks this is about the
+// first chunk only: the others are copied by the workgroups at the front of the grid, which start before any workgroup that
+// waits and wait for nobody themselves.
 template <int DEPTH>
 __device__ __forceinline__ void consumer_wait_shared(const AgProducer& p, unsigned long long chan_mask, int tid, int nthreads, int* s_state) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -177,7 +181,7 @@ __device__ __forceinline__ void consumer_wait_shared(const AgProducer& p, unsign
       missing = __builtin_amdgcn_ballot_w64(mine && (int)(f - p.wait_target) < 0);
       if (!missing) break;
       const unsigned long long waited = wall_clock64() - t0;
-      if (waited > kShareGrace) { give_up = 1; break; }
+      if (waited > p.share_patience) { give_up = 1; break; }
       __builtin_amdgcn_s_sleep(2);
     }
     *s_state = give_up;
@@ -189,11 +193,17 @@ __device__ __forceinline__ void consumer_wait_shared(const AgProducer& p, unsign
     missing = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(s_state[1]) | ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(s_state[2]) << 32);
     const int rows = p.rows_per_channel, cols = p.k_chunks > 1 ? p.Tn_p : p.ld;
     for (; missing; missing &= missing - 1) {
-      const int row_lo = __builtin_ctzll(missing) * rows, src = row_lo / p.rows_per_rank;
-      if (!(src == p.rank && p.local_in_place))
-        for (int r = 0; r < rows; r += p.Tm_p)   // (a piece of a tile mover spans less than 2 GiB)
-          copy_tile<DEPTH>(p.shards[src] + (long)(row_lo + r - src * p.rows_per_rank) * p.ld, p.ld, p.gathered + (long)(row_lo + r) * p.ld, p.ld, p.Tm_p, cols, tid,
-                           nthreads);
+      const int ch = __builtin_ctzll(missing), row_lo = ch * rows, src = row_lo / p.rows_per_rank;
+      if (src == p.rank && p.local_in_place) continue;
+      for (int r = 0; r < rows; r += p.Tm_p) {   // (a piece of a tile mover spans less than 2 GiB)
+        if (wave == 0) *s_state = (int)(__hip_atomic_load(p.flags + ch * p.k_chunks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - p.wait_target) >= 0;
+        __syncthreads();
+        const int arrived = __builtin_amdgcn_readfirstlane(*s_state);
+        __syncthreads();
+        if (arrived) break;
+        copy_tile<DEPTH>(p.shards[src] + (long)(row_lo + r - src * p.rows_per_rank) * p.ld, p.ld, p.gathered + (long)(row_lo + r) * p.ld, p.ld, p.Tm_p, cols, tid,
+                         nthreads);
+      }
     }
     wait_all_vmem();
   }

@@ -846,6 +846,8 @@ static int ag_gemm_impl(tl_ctx* ctx, const void* const* a_shards, void* a_gather
   const bool alone = cfg.comm_alone != 0;  // communication side only (timing)
   // shares: the whole launch has to fit on the chip at once (and nothing but the gather itself is to be done)
   const bool share = r.fold && !alone && !peer_slots && G + r.n_comm <= ctx->num_cus && (r.k_chunks == 1 || r.n_comm >= 16);
+  // 200 us, and what the copies take at 1 TB/s (they reach 1.8 TB/s beside the GEMM)
+  if (share) p.prod.share_patience = 20000u + (unsigned)(2.0 * M * K / 1e4);
   if (r.k_chunks > 1 && cfg.comm_mode != TL_COMM_WAVES && cfg.comm_mode != TL_COMM_SIDE_KERNEL) r.k_chunks = 1;
   if (alone && (cfg.comm_mode == TL_COMM_NONE || cfg.comm_mode == TL_COMM_EXTERNAL))
     return fail(TL_ERR_INVALID_ARG, "tl_ag_gemm: comm_alone needs a comm_mode in which the library runs a producer");

@@ -93,3 +93,37 @@ def test_a_share_that_never_arrives_is_fetched_by_who_needs_it():
     a_ref, _, c_ref = ops.ag_gemm(w["a_shards"], w["b"])
     assert np.array_equal(down(gathered), a_ref)
     assert_close_bf16(down(c), c_ref, "self-served gather")
+
+
+def test_a_long_gather_by_shares_is_not_done_twice():
+    """1 GiB in one round of workgroups, several times the patience a small gather gets: no slower than twice the same call
+    with the producers' queue (if all workgroups lose patience together, it takes more than five times as long)."""
+    M, N, K, R = 65536, 256, 8192, 8
+    g = torch.Generator(device=dev())
+    g.manual_seed(165)
+    shards = [torch.randn(M // R, K, generator=g, device=dev(), dtype=torch.bfloat16) for _ in range(R)]
+    b = torch.randn(K, N, generator=g, device=dev(), dtype=torch.bfloat16) * 0.02
+    ref = torch.cat([s.float() @ b.float() for s in shards])
+    best = {}
+    for wg in (0, 64):
+        ctx = make_ctx(world_size=R, rank=3, comm_mode=tl.TL_COMM_SIDE_KERNEL, comm_workgroups=wg)
+        ws_bytes, n_flags = tl.tl_query_workspace(ctx, tl.TL_OP_AG_GEMM, [M, N, K])
+        gathered, c = torch.zeros(M, K, device=dev(), dtype=torch.bfloat16), torch.zeros(M, N, device=dev(), dtype=torch.bfloat16)
+        flags, wsp = torch.zeros(n_flags, dtype=torch.int32, device=dev()), torch.zeros(ws_bytes // 4, dtype=torch.int32, device=dev())
+        comm = torch.cuda.Stream()
+        times = []
+        for epoch in range(1, 5):
+            torch.cuda.synchronize()
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            tl.tl_ag_gemm(ctx, shards, gathered, b, c, M, N, K, flags, epoch, wsp, ws_bytes, torch.cuda.current_stream(), comm)
+            torch.cuda.current_stream().wait_stream(comm)
+            e1.record()
+            torch.cuda.synchronize()
+            tl.tl_check_status(ctx, wsp)
+            times.append(e0.elapsed_time(e1))
+        best[wg] = min(times)
+        assert all(torch.equal(gathered[q * (M // R):(q + 1) * (M // R)], shards[q]) for q in range(R))
+        assert float((c.float() - ref).norm() / ref.norm()) < 5e-3
+        tl.tl_ctx_destroy(ctx)
+    assert best[0] < 2 * best[64], best
