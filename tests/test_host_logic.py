@@ -1,6 +1,9 @@
 """Host-side logic of the library without a GPU: a context made by tl_ctx_create_host answers the geometry queries and
 the schedule dump (paper: "Tile-Centric Mapping"), which are compared with the mapping oracle here as the GPU tests do
 on the device context; shapes the mapping cannot serve are refused before anything could be enqueued."""
+import random
+import time
+
 import pytest
 
 import paper_2503_20313_amd as tl
@@ -170,4 +173,55 @@ def test_communication_alone_has_workgroups(mode, M, N, K):
     """Also where the tiles of the GEMM, which does not run, would fill the chip."""
     ctx = host_ctx(world_size=8, comm_mode=mode, comm_alone=1)
     assert tl.tl_resolve(ctx, tl.TL_OP_AG_GEMM, [M, N, K])["comm_workgroups"] >= 8
+    tl.tl_ctx_destroy(ctx)
+
+
+def producer_tile_by_every_divisor(rows, ld, total, workers):
+    """The producer tile the library's comment asks for, over all divisors in ascending order."""
+    want = total // workers
+    if want > 65536:
+        want = max(want // 2, 65536)
+    want = min(max(want, 16384), 262144)
+    best = None
+    for tm in range(1, rows + 1):
+        if rows % tm:
+            continue
+        tn, cost = ld, 1.0
+        while True:
+            size = 2 * tm * tn
+            c = cost * (size / want if size > want else want / size)
+            if best is None or c < best[0]:
+                best = (c, tm, tn)
+            if tn % 16 or tn // 2 < 64:
+                break
+            tn, cost = tn // 2, 1.5
+    return best[1:]
+
+
+def test_producer_tile_is_the_best_divisor():
+    rng = random.Random(19)
+    shapes = [(R, C, R * C * rng.choice([1, 2, 67, 128, 360, 1024, 1260, rng.randrange(1, 3000)]), 8 * rng.choice([1, 16, 125, 512, 1024, rng.randrange(1, 1200)]))
+              for R, C in rng.choices([(1, 1), (2, 1), (4, 2), (8, 4), (7, 3)], k=150)]
+    for R, C, M, K in shapes:
+        ctx = host_ctx(world_size=R, channels_per_rank=C)
+        info = tl.tl_resolve(ctx, tl.TL_OP_AG_GEMM, [M, 512, K])
+        assert (info["comm_tile_m"], info["comm_tile_n"]) == producer_tile_by_every_divisor(M // (R * C), K, 2 * M * K, CUS), (R, C, M, K)
+        tl.tl_ctx_destroy(ctx)
+
+
+def test_geometry_does_not_take_longer_for_more_rows():
+    """Every call works its geometry out: 2^20 rows per channel, where trying every number up to that takes a thousand times
+    as long as for 2^10, in the time of the square root at most (32 times; the fixed part makes it far less)."""
+    ctx = host_ctx()
+
+    def best_of(M):
+        times = []
+        for _ in range(30):
+            t0 = time.perf_counter()
+            tl.tl_resolve(ctx, tl.TL_OP_AG_GEMM, [M, 512, 512])
+            times.append(time.perf_counter() - t0)
+        return min(times)
+
+    small, large = best_of(1 << 10), best_of(1 << 20)
+    assert large < 32 * small, (small, large)
     tl.tl_ctx_destroy(ctx)
