@@ -397,15 +397,24 @@ int fail(int code, const char* fmt, ...) {
 // the communication side, overlaps the remaining GEMM tiles and only a push is left at the end).
 static int rs_first_rank(const tl_config& c) { return c.tile_order >= TL_ORDER_OWN_FIRST ? c.rank : (c.rank + 1) % c.world_size; }
 
+// Communication workgroups.  In-kernel ones each take a compute unit's worth of LDS and registers; as a kernel of their
+// own they are small and share compute units with the GEMM, so many more of them pay off (the reduce side: one workgroup
+// per compute unit, each is bound by the bytes it keeps in flight).
+static int comm_workgroups(const tl_config& c, int op) {
+  if (c.comm_workgroups > 0) return c.comm_workgroups;
+  return c.comm_mode == TL_COMM_WAVES ? 16 : (op == TL_OP_GEMM_RS ? 256 : 128);
+}
+
 // Time of a GEMM on the two square tile shapes, in microseconds, for choosing between them and for the number of
 // workgroups that share a tile: every round of workgroups costs the fixed part of a tile (first loads, epilogue, store)
 // and its K steps of 64, and a step takes the longer the more compute units are busy (they share the memory side and the
 // power limit).  Fitted to timings of this kernel without communication: 256x256 with K = 8192 takes 123 / 156 / 214 us
 // on 1 / 128 / 256 compute units, K = 1024 24 / 29 / 37 us; 128x128 40 / 52 / 66 us on 1 / 112 / 256, 10 / 12 / 14 us.
-static double tile_rounds_us(bool large, long workgroups, double steps, int cus) {
+// `room` is how many workgroups the GEMM has on the chip at once, out of `cus`.
+static double tile_rounds_us(bool large, long workgroups, double steps, int room, int cus) {
   auto round = [&](double busy) { return large ? 6.5 + steps * (0.92 + 0.70 * busy) : 3.5 + steps * (0.30 + 0.19 * busy); };
-  const long full = workgroups / cus, rest = workgroups % cus;
-  return full * round(1.0) + (rest ? round((double)rest / cus) : 0.0);
+  const long full = workgroups / room, rest = workgroups % room;
+  return full * round((double)room / cus) + (rest ? round((double)rest / cus) : 0.0);
 }
 
 constexpr int kMaxSplits = 8;
@@ -414,12 +423,25 @@ constexpr int kMaxSplits = 8;
 // memory and the count, then the slots it reads -- is about 2 us + 0.8 us a slot.
 static int choose_splits(long tiles, int K, int cus, double* us) {
   int best = 1;
-  *us = tile_rounds_us(false, tiles, K / 64.0, cus);
+  *us = tile_rounds_us(false, tiles, K / 64.0, cus, cus);
   for (int S = 2; S <= kMaxSplits && tiles * S <= cus && K >= 1024 * S; S++) {
-    const double t = tile_rounds_us(false, tiles * S, K / 64.0 / S, cus) + 2.0 + 0.8 * S;
+    const double t = tile_rounds_us(false, tiles * S, K / 64.0 / S, cus, cus) + 2.0 + 0.8 * S;
     if (t < *us) { *us = t; best = S; }
   }
   return best;
+}
+
+// Time of the reduce side inside the GEMM launch (TL_COMM_WAVES): its workgroups have as many threads as the tile, and
+// what each moves is bound by the bytes those keep in flight: with 256 threads about 8.5 KB a microsecond where it sums
+// the own segment over all ranks (7 at two ranks, 10 at eight), 22 where it adds two sources at a time and copies (the
+// ring, and segments that the tiles do not push themselves); twice that with 512.  It lasts well beyond the GEMM, and
+// counts in full beside it.  Measured at 8 ranks with 16 such workgroups, 128x128 against 256x256: [2048,256] x [256,2048]
+// 67 against 53 us, K = 1792 84 / 75, K = 3584 100 / 102; [512,3584] x [3584,4608] 74 / 93; [1024,256] x [256,8192]
+// 124 / 74.  The choice by the sum of both times is within 7 % of the better one in all but 5 of 288 shapes (ring and not).
+static double reduce_us(const tl_config& c, long M, long N, int n_comm, bool large) {
+  const double all = (double)M * N * 2, own = all / c.world_size;
+  const double us = c.rs_direct_push ? (c.world_size + 1) * own / 8.5e3 : 3.0 * all / 22.0e3;
+  return us / (large ? 2 * n_comm : n_comm);
 }
 
 // Scratch of a call whose tiles are shared (after the first 256 bytes of the workspace): counters, then slots.  The
@@ -453,9 +475,20 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     if (v < 0) return fail(TL_ERR_UNSUPPORTED_SHAPE, "compute tile %dx%d is not one of 256x256, 256x224, 128x128", c.tile_m, c.tile_n);
   } else {
     const long n_small = (long)ceil_div(M, 128) * ceil_div(N, 128), n_large = (long)ceil_div(M, 256) * ceil_div(N, 256);
-    double us_small = tile_rounds_us(false, n_small, K / 64.0, ctx->num_cus);
-    if (op == TL_OP_AG_GEMM) splits = choose_splits(n_small, K, ctx->num_cus, &us_small);
-    if (us_small < tile_rounds_us(true, n_large, K / 64.0, ctx->num_cus)) v = TILE_128x128;
+    const bool waves_rs = op == TL_OP_GEMM_RS && c.comm_mode == TL_COMM_WAVES;
+    const int cus = ctx->num_cus, n_comm = comm_workgroups(c, op);
+    int room = c.compute_workgroups > 0 && c.compute_workgroups < cus ? c.compute_workgroups : cus;
+    if (waves_rs && room > cus - n_comm) room = cus - n_comm > 1 ? cus - n_comm : 1;   // the reduce workgroups keep a compute unit each
+    double us_small = tile_rounds_us(false, n_small, K / 64.0, room, cus), us_large = tile_rounds_us(true, n_large, K / 64.0, room, cus);
+    if (op == TL_OP_AG_GEMM && c.compute_workgroups == 0 && c.comm_mode != TL_COMM_STREAM) splits = choose_splits(n_small, K, cus, &us_small);
+    if (waves_rs) {
+      us_small += reduce_us(c, M, N, n_comm, false);
+      us_large += reduce_us(c, M, N, n_comm, true);
+    }
+    // A reduce side that moves every segment slows the small tile down from its second round on, in either binding: ring,
+    // side kernel, 128x128 against 256x256 (us): 256 tiles, K = 1792 60 / 69; 288 76 / 66; 512 86 / 73; 1152 202 / 137.
+    const bool one_round_only = op == TL_OP_GEMM_RS && c.comm_mode != TL_COMM_NONE && !c.rs_direct_push;
+    if (us_small < us_large && !(one_round_only && n_small > room)) v = TILE_128x128;
     else splits = 1;
   }
   if (v < 0) {
@@ -485,7 +518,7 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
   if (c.compute_workgroups == 0 && c.comm_mode == TL_COMM_STREAM && op == TL_OP_AG_GEMM && G > 32) G -= 16;
   if (G > r->n_tiles) G = r->n_tiles;
   r->G = G;
-  r->splits = c.compute_workgroups == 0 && c.comm_mode != TL_COMM_STREAM && G == r->n_tiles ? splits : 1;
+  r->splits = splits;
   {
     // group of row blocks walked together: a power of two that keeps a group inside one rank's rows
     int per_rank = (r->nbm % R == 0) ? r->nbm / R : r->nbm;
@@ -497,11 +530,7 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     if (gm > r->nbm) gm = r->nbm;
     r->group_m = gm;
   }
-  // in-kernel communication workgroups each take a compute unit's worth of LDS and registers; as a kernel of
-  // their own they are small and share compute units with the GEMM, so many more of them pay off
-  // (the reduce side as a kernel of its own: one workgroup per compute unit, each is bound by the bytes it keeps in flight)
-  int n_comm = c.comm_workgroups > 0 ? c.comm_workgroups : (c.comm_mode == TL_COMM_WAVES ? 16 : (op == TL_OP_GEMM_RS ? 256 : 128));
-  r->n_comm = (c.comm_mode == TL_COMM_NONE) ? 0 : n_comm;
+  r->n_comm = c.comm_mode == TL_COMM_NONE ? 0 : comm_workgroups(c, op);
   // ---- communication tiles
   if (op == TL_OP_AG_GEMM) {
     const int C = c.channels_per_rank;

@@ -225,3 +225,28 @@ def test_geometry_does_not_take_longer_for_more_rows():
     small, large = best_of(1 << 10), best_of(1 << 20)
     assert large < 32 * small, (small, large)
     tl.tl_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("op,mode,dims,kw,tile", [
+    # the reduce workgroups inside the launch take twice as long with the small tile's threads (measured, 128 against 256):
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_WAVES, [2048, 2048, 768], dict(rs_direct_push=1), 256),      # 76 / 57 us
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_WAVES, [1024, 8192, 256], dict(rs_direct_push=1), 256),      # 124 / 74
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_WAVES, [4096, 4608, 1792], dict(rs_direct_push=1), 256),     # 286 / 182
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_WAVES, [512, 4608, 3584], dict(rs_direct_push=1), 128),      # 74 / 93
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_WAVES, [1024, 1024, 3584], dict(rs_direct_push=1), 128),     # 54 / 78
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_WAVES, [1024, 2048, 3584], dict(), 128),                     # ring: 72 / 92
+    # ... and not at all as a kernel of their own
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_SIDE_KERNEL, [2048, 2048, 1792], dict(rs_direct_push=1), 128),
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_SIDE_KERNEL, [4096, 2048, 1792], dict(rs_direct_push=1), 128),   # 56 / 74
+    # a reduce side that moves every segment: one round of small tiles only (ring)
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_SIDE_KERNEL, [2048, 2048, 1792], dict(), 128),               # 61 / 69
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_SIDE_KERNEL, [4096, 2048, 1792], dict(), 256),               # 86 / 74
+    (tl.TL_OP_GEMM_RS, tl.TL_COMM_SIDE_KERNEL, [4096, 4608, 1792], dict(), 256),               # 202 / 137
+    # the GEMM has no more compute units than it is given
+    (tl.TL_OP_AG_GEMM, tl.TL_COMM_SIDE_KERNEL, [2048, 2048, 8192], dict(), 128),
+    (tl.TL_OP_AG_GEMM, tl.TL_COMM_SIDE_KERNEL, [2048, 2048, 8192], dict(compute_workgroups=64), 256),
+])
+def test_tile_shape_counts_what_else_the_call_does(op, mode, dims, kw, tile):
+    ctx = host_ctx(world_size=8, comm_mode=mode, **kw)
+    assert tl.tl_resolve(ctx, op, dims)["tile_m"] == tile
+    tl.tl_ctx_destroy(ctx)
