@@ -36,6 +36,7 @@ struct GemmRsParams {
   int K;
   Sched sched;
   int n_comm, do_compute, do_notify;
+  int comm_at;          // where the reduce workgroups stand in the grid: 0, or behind the GEMM's
 };
 
 // consumer_tile_wait inside the K loop, for AllGather channels that arrive in chunks along K: K step ks opens chunk
@@ -171,13 +172,14 @@ template <class Cfg>
 __global__ void __launch_bounds__(Cfg::NTHREADS) gemm_rs_kernel(const GemmRsParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x;
-  if ((int)blockIdx.x < p.n_comm) {
-    rs_consumer(p.rs, blockIdx.x, p.n_comm, tid, Cfg::NTHREADS);
+  const int comm_wg = (int)blockIdx.x - p.comm_at;
+  if (comm_wg >= 0 && comm_wg < p.n_comm) {
+    rs_consumer(p.rs, comm_wg, p.n_comm, tid, Cfg::NTHREADS);
     return;
   }
   if (!p.do_compute) return;
   __builtin_amdgcn_s_setprio(TL_COMPUTE_WAVE_PRIO);  // matrix waves go first when they share a SIMD with communication waves
-  const int w = blockIdx.x - p.n_comm;
+  const int w = p.comm_at ? blockIdx.x : blockIdx.x - p.n_comm;
   const RsSide& rs = p.rs;
   const ClockSample cs0 = clock_sample_begin(w);
   // the 224-wide tile has no register left for the state a deferred notification carries from tile to tile
@@ -478,12 +480,12 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     const bool waves_rs = op == TL_OP_GEMM_RS && c.comm_mode == TL_COMM_WAVES;
     const int cus = ctx->num_cus, n_comm = comm_workgroups(c, op);
     int room = c.compute_workgroups > 0 && c.compute_workgroups < cus ? c.compute_workgroups : cus;
-    if (waves_rs && room > cus - n_comm) room = cus - n_comm > 1 ? cus - n_comm : 1;   // the reduce workgroups keep a compute unit each
+    if (waves_rs && !reduce_behind_gemm(n_comm, cus) && room > cus - n_comm) room = cus - n_comm;   // the reduce workgroups keep a compute unit each
     double us_small = tile_rounds_us(false, n_small, K / 64.0, room, cus), us_large = tile_rounds_us(true, n_large, K / 64.0, room, cus);
     if (op == TL_OP_AG_GEMM && c.compute_workgroups == 0 && c.comm_mode != TL_COMM_STREAM) splits = choose_splits(n_small, K, cus, &us_small);
     if (waves_rs) {
-      us_small += reduce_us(c, M, N, n_comm, false);
-      us_large += reduce_us(c, M, N, n_comm, true);
+      us_small += reduce_us(c, M, N, n_comm < cus ? n_comm : cus, false);
+      us_large += reduce_us(c, M, N, n_comm < cus ? n_comm : cus, true);
     }
     // A reduce side that moves every segment slows the small tile down from its second round on, in either binding: ring,
     // side kernel, 128x128 against 256x256 (us): 256 tiles, K = 1792 60 / 69; 288 76 / 66; 512 86 / 73; 1152 202 / 137.
@@ -1029,6 +1031,7 @@ static int gemm_rs_impl(const char* name, bool ring, tl_ctx* ctx, const void* a,
     case TL_COMM_WAVES:
       if (int e = peers_arrive(alone ? cs : ms)) return e;
       p.n_comm = r.n_comm; p.do_notify = alone ? 0 : 1; p.rs.do_wait = alone ? 0 : 1;
+      p.comm_at = !alone && reduce_behind_gemm(r.n_comm, ctx->num_cus) ? r.G : 0;
       return launch_gemm_rs(r.variant, p, alone ? r.n_comm : r.G + r.n_comm, cs);
     case TL_COMM_EXTERNAL:
       return fail(TL_ERR_INVALID_ARG, "%s: TL_COMM_EXTERNAL is not defined for this operator", name);

@@ -69,6 +69,12 @@ typedef TileCfg<64, 256, 2, 4, 32, 7> Cfg64x256;
 static const int kThreads[TILE_VARIANTS] = {Cfg256x256::NTHREADS, Cfg256x224::NTHREADS, Cfg128x128::NTHREADS};
 static const int kLds[TILE_VARIANTS] = {Cfg256x256::LDS_BYTES, Cfg256x224::LDS_BYTES, Cfg128x128::LDS_BYTES};
 
+// Reduce workgroups inside the GEMM launch (TL_COMM_WAVES) wait for its tiles, and every one keeps a compute unit: the
+// kernels' LDS lets no second workgroup beside it.  In front of the grid they overlap with the GEMM, as long as they leave
+// the workgroups they wait for a place to run; more than half the chip's worth of them go behind the GEMM's workgroups,
+// which wait for nobody (with 248 in front, one compute unit a die left over, waits of 5 s expired).
+inline bool reduce_behind_gemm(int n_comm, int cus) { return 2 * n_comm > cus; }
+
 inline bool aligned128(const void* p) { return ((uintptr_t)p & 127) == 0; }
 
 inline WaitCtl make_ctl(const tl_ctx* ctx, void* workspace) {

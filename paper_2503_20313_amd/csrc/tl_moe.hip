@@ -427,7 +427,8 @@ struct MoeP2Params {
   unsigned epoch;
   unsigned* rows_ready;     // [T/Tt * nbn] rows delivered per (token block, column block)
   RsSide rs;                // on partial [T,H]; rs.ready is raised by stage B
-  int n_topk, n_rs;         // workgroups of stage B and C (in front of the grid when fused)
+  int n_topk, n_rs;         // workgroups of stage B and C in this launch
+  int comm_at;              // where they stand in the grid: 0, or behind the GEMM's
   int do_compute, do_notify, do_wait;
   int gb;  // column blocks walked side by side by stages A and B
 };
@@ -503,17 +504,18 @@ template <class Cfg>
 __global__ void __launch_bounds__(Cfg::NTHREADS) moe_gemm_scatter_kernel(const MoeP2Params p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x;
-  if ((int)blockIdx.x < p.n_topk) {
-    topk_reduce(p, blockIdx.x, p.n_topk, tid, Cfg::NTHREADS);
+  const int comm_wg = (int)blockIdx.x - p.comm_at;
+  if (comm_wg >= 0 && comm_wg < p.n_topk) {
+    topk_reduce(p, comm_wg, p.n_topk, tid, Cfg::NTHREADS);
     return;
   }
-  if ((int)blockIdx.x < p.n_topk + p.n_rs) {
-    rs_consumer(p.rs, blockIdx.x - p.n_topk, p.n_rs, tid, Cfg::NTHREADS);
+  if (comm_wg >= 0 && comm_wg < p.n_topk + p.n_rs) {
+    rs_consumer(p.rs, comm_wg - p.n_topk, p.n_rs, tid, Cfg::NTHREADS);
     return;
   }
   if (!p.do_compute) return;
   __builtin_amdgcn_s_setprio(TL_COMPUTE_WAVE_PRIO);  // matrix waves go first when they share a SIMD with communication waves
-  const int w = blockIdx.x - p.n_topk - p.n_rs;
+  const int w = p.comm_at ? blockIdx.x : blockIdx.x - p.n_topk - p.n_rs;
   Sched sc;
   sc.nbm = *p.n_row_tiles;
   sc.nbn = p.nbn;
@@ -868,6 +870,7 @@ int tl_moe_gemm_scatter_rs(tl_ctx* ctx, const void* x2, const void* w2, const in
     case TL_COMM_WAVES:
       if (int e = launch_peers_arrive(p.rs, alone ? cs : ms)) return e;
       p.n_topk = n_topk; p.n_rs = n_rs; p.do_notify = alone ? 0 : 1; p.do_wait = alone ? 0 : 1;
+      p.comm_at = !alone && reduce_behind_gemm(n_topk + n_rs, ctx->num_cus) ? r.G : 0;
       return launch(alone ? n_topk + n_rs : r.G + n_topk + n_rs);
     case TL_COMM_SIDE_KERNEL:
       p.n_topk = 0; p.n_rs = 0; p.do_notify = alone ? 0 : 1; p.do_wait = alone ? 0 : 1;

@@ -107,6 +107,16 @@ def test_ragged_and_mismatched_reduce_tiles(tile, rt, direct):
         assert pushed[q].tolist() == [0 if q == 1 else 2] * tps, f"pushed counters of segment {q}"
 
 
+@pytest.mark.parametrize("wgs", [128, 129, 300])
+@pytest.mark.parametrize("direct", [0, 1, 2])
+def test_more_reduce_workgroups_than_compute_units(wgs, direct):
+    """256 reduce tiles and up to more workgroups to wait for them than the chip holds beside the GEMM's: in front of the
+    GEMM's workgroups up to half the chip, behind them from there on."""
+    w = wl.gemm_rs_inputs(2048, 2048, 64, 8, 3, config_id=28)
+    ha, partial, push, out, flags, info = run_gemm_rs(w, tl.TL_COMM_WAVES, epochs=2, comm_workgroups=wgs, tile_m=128, tile_n=128, rs_direct_push=direct)
+    check(w, ha, partial, push, out, f"{wgs} reduce workgroups, direct={direct}", direct=bool(direct))
+
+
 def test_default_reduce_tile_divides_the_segment():
     """M/R = 224 rows per segment, no reduce tile given: the library picks a row count that divides the segment (112
     under 128-row GEMM tiles) instead of refusing the shape."""

@@ -233,6 +233,13 @@ def test_part2_small(mode, rank, direct):
     run_part2(w, MODES[mode], epochs=2, comm_workgroups=4, rs_direct_push=direct)
 
 
+def test_part2_more_reduce_workgroups_than_compute_units():
+    """As many workgroups of the reduce stages as the chip has compute units, and more: they stand behind the GEMM's."""
+    w = wl.moe_inputs(2048, 1024, 64, 4, 2, 4, 1, config_id=48)
+    for tile in (128, 256):
+        run_part2(w, tl.TL_COMM_WAVES, epochs=2, comm_workgroups=300, comm_tile_m=32, tile_m=tile, tile_n=tile, rs_direct_push=1)
+
+
 def test_part2_gemm_stage_only_and_other_shapes():
     w = wl.moe_inputs(640, 512, 192, 5, 3, 5, 3, config_id=45)
     run_part2(w, tl.TL_COMM_NONE)
