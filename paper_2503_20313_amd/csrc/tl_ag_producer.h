@@ -262,7 +262,7 @@ __device__ __forceinline__ void ag_producer(const AgProducer& p, int tid, int nt
 template <int DEPTH = 2, bool ONE = false>
 __device__ __forceinline__ void consumer_wait_or_produce(const AgProducer& p, unsigned long long chan_mask, int tid, int nthreads, int* s_ticket) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int first = __builtin_ctzll(chan_mask);
+  const int first = ONE || chan_mask ? __builtin_ctzll(chan_mask) : 0;   // (no channel: nothing to wait for, but a flag to look at)
   unsigned long long t0 = 0;
   if (wave == 0 && (p.ctl.timeout || p.pace_q8)) t0 = wall_clock64();
   // Tickets are taken only while the queue head has not passed the last tile of the awaited channels: beyond that point every

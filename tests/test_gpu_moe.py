@@ -114,6 +114,29 @@ def test_part1_small(mode):
 
 
 @pytest.mark.parametrize("mode", ["waves", "side"])
+def test_part1_tiles_that_wait_for_no_channel(mode):
+    """Tile tables with empty channel masks: the token rows are in place already, no tile waits (and the producers write the
+    same bytes again)."""
+    w = wl.moe_inputs(256, 128, 192, 4, 2, 2, 0, config_id=49)
+    T, H, I, E, k, R = 256, 128, 192, 4, 2, 2
+    ctx = make_ctx(world_size=R, rank=1, channels_per_rank=2, comm_mode=MODES[mode])
+    q = tl.tl_moe_query(ctx, tl.TL_OP_MOE_AG_GATHER_GEMM, T, H, I, E, k)
+    ids, tw, off, srow, tab, nt = route_on_gpu(ctx, w["logits"], T, E, k, q["tile_m"], q["max_row_tiles"])
+    tab[:, 3:5] = 0
+    shards = [up(s) for s in w["x_shards"]]
+    xg, w1, y1 = up(np.concatenate(w["x_shards"])), up(w["w1"].reshape(E * H, I)), poison((T * k, I))
+    flags = torch.zeros(q["n_flags"], dtype=torch.int32, device=dev())
+    wsp = torch.zeros(q["ws_bytes"] // 4, dtype=torch.int32, device=dev())
+    torch.cuda.synchronize()
+    tl.tl_moe_ag_gather_gemm(ctx, shards, xg, w1, srow, tab, nt, y1, T, H, I, E, k, flags, 1, wsp, q["ws_bytes"])
+    torch.cuda.synchronize()
+    tl.tl_check_status(ctx, wsp)
+    tl.tl_ctx_destroy(ctx)
+    y_ref = ops.moe_ag_gather_gemm(w["x_shards"], w["w1"], srow.cpu().numpy(), off.cpu().numpy(), k)[2]
+    assert_close_bf16(down(y1), y_ref, "no channels")
+
+
+@pytest.mark.parametrize("mode", ["waves", "side"])
 def test_part1_simulated_links(mode):
     """Token shards arriving over simulated links (interleaved queue, paced tiles, consumers only wait): same results."""
     w = wl.moe_inputs(512, 128, 192, 4, 2, 4, 1, config_id=44)
