@@ -407,6 +407,13 @@ static int comm_workgroups(const tl_config& c, int op) {
   return c.comm_mode == TL_COMM_WAVES ? 16 : (op == TL_OP_GEMM_RS ? 256 : 128);
 }
 
+// Persistent GEMM workgroups before the number of tiles limits them.  The runtime's copy path runs as kernels too, and a
+// grid that fills every compute unit while it waits for those copies would keep them from ever starting: leave some free.
+static int default_grid(const tl_config& c, int op, int cus) {
+  if (c.compute_workgroups > 0) return c.compute_workgroups;
+  return c.comm_mode == TL_COMM_STREAM && op == TL_OP_AG_GEMM && cus > 32 ? cus - 16 : cus;
+}
+
 // Time of a GEMM on the two square tile shapes, in microseconds, for choosing between them and for the number of
 // workgroups that share a tile: every round of workgroups costs the fixed part of a tile (first loads, epilogue, store)
 // and its K steps of 64, and a step takes the longer the more compute units are busy (they share the memory side and the
@@ -479,7 +486,7 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     const long n_small = (long)ceil_div(M, 128) * ceil_div(N, 128), n_large = (long)ceil_div(M, 256) * ceil_div(N, 256);
     const bool waves_rs = op == TL_OP_GEMM_RS && c.comm_mode == TL_COMM_WAVES;
     const int cus = ctx->num_cus, n_comm = comm_workgroups(c, op);
-    int room = c.compute_workgroups > 0 && c.compute_workgroups < cus ? c.compute_workgroups : cus;
+    int room = default_grid(c, op, cus) < cus ? default_grid(c, op, cus) : cus;
     if (waves_rs && !reduce_behind_gemm(n_comm, cus) && room > cus - n_comm) room = cus - n_comm;   // the reduce workgroups keep a compute unit each
     double us_small = tile_rounds_us(false, n_small, K / 64.0, room, cus), us_large = tile_rounds_us(true, n_large, K / 64.0, room, cus);
     if (op == TL_OP_AG_GEMM && c.compute_workgroups == 0 && c.comm_mode != TL_COMM_STREAM) splits = choose_splits(n_small, K, cus, &us_small);
@@ -514,10 +521,7 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
   r->n_tiles = r->nbm * r->nbn;
   r->rows_per_rank = M / R;
   // ---- grid
-  int G = c.compute_workgroups > 0 ? c.compute_workgroups : ctx->num_cus;
-  // The runtime's copy path runs as kernels too, and a persistent GEMM grid that fills every compute unit while it
-  // waits for those copies would keep them from ever starting: leave some compute units free for them.
-  if (c.compute_workgroups == 0 && c.comm_mode == TL_COMM_STREAM && op == TL_OP_AG_GEMM && G > 32) G -= 16;
+  int G = default_grid(c, op, ctx->num_cus);
   if (G > r->n_tiles) G = r->n_tiles;
   r->G = G;
   r->splits = splits;
