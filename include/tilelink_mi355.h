@@ -52,7 +52,8 @@ enum { TL_COMM_NONE = 0,   /* data already in place: no producer runs, consumers
        TL_COMM_STREAM = 2, /* host-side: copies and notifications enqueued on comm_stream through the runtime's
                               copy path (rank_copy_data + rank_notify); reduce work runs as a second kernel there */
        TL_COMM_SIDE_KERNEL = 3, /* device-side copy/reduce workgroups launched as a small-footprint kernel of their
-                              own on comm_stream, so that they can share compute units with resident GEMM workgroups */
+                              own on comm_stream, so that they can share compute units with resident GEMM workgroups;
+                              tl_ag_gemm takes its copy workgroups into the GEMM's launch instead (see there) */
        TL_COMM_EXTERNAL = 4, /* consumers wait on the flags but the library runs no producer: the caller (a peer,
                               another library) moves the data and raises the flags itself */
        TL_COMM_COPY_ENGINE = 5 /* tl_ag_gemm family: as TL_COMM_STREAM, but every shard copy is handed to a copy (DMA) engine,
@@ -85,7 +86,9 @@ typedef struct tl_config {
   int comm_tile_m;         /* producer row-tile Tm_p (AllGather) / reduce row-tile (ReduceScatter); 0 = auto */
   int comm_tile_n;         /* producer column-tile Tn_p; 0 = whole row */
   int comm_mode;           /* TL_COMM_* */
-  int comm_workgroups;     /* workgroups given to communication in TL_COMM_WAVES (paper's examples: 20 SMs); 0 = auto */
+  int comm_workgroups;     /* workgroups given to communication in TL_COMM_WAVES and SIDE_KERNEL (paper's examples: 20 SMs);
+                              0 = auto.  In TL_COMM_WAVES the ReduceScatter operators put them in front of the GEMM's
+                              workgroups, or behind them where they are more than half as many as the compute units */
   int compute_workgroups;  /* persistent compute workgroups G; 0 = number of compute units */
   int tile_order;          /* TL_ORDER_* */
   int xcd_swizzle;         /* 1: workgroups on one die take neighbouring tiles (see tl_dump_schedule) */
@@ -108,7 +111,8 @@ typedef struct tl_config {
                               further chunk when its K loop reaches it (the decoupled tile sizes of the paper's
                               "tile size" sub-space, applied along K).  Needs K divisible by 64*ag_k_chunks with at
                               least 8 K steps of 64 per chunk, comm_tile_n 0, and TL_COMM_WAVES or TL_COMM_SIDE_KERNEL
-                              with the 256x256 compute tile; elsewhere, and for 0 or 1, one flag per channel. */
+                              with the 256x256 compute tile; elsewhere -- also where the library's own choice is another
+                              tile, which tl_resolve reports --, and for 0 or 1, one flag per channel. */
   int link_gbps;           /* AllGather operators: 0 = the producers copy as fast as they can.  > 0 = simulated links: every
                               other rank's shard arrives at this many GB/s (decimal), all ranks side by side, starting
                               when the call's first producer starts; a producer tile of a remote shard is not copied
@@ -418,6 +422,8 @@ int tl_attn_query(const tl_ctx* ctx, int S, int heads, int head_dim, int causal,
  *                   (inclusive ranges of reduce tiles notified), followed by 9 ints per reduce tile in the
  *                   order the reduce workgroups visit them: rs_tile_id, cm, cn, row_lo, row_hi, col_lo, col_hi,
  *                   dest_rank, expected.
+ * Where several workgroups share a tile of tl_ag_gemm along K, the records are those of the call with whole tiles: which
+ * tiles there are, the rows and channels of each, and one workgroup per tile, as tl_resolve counts them.
  * `cap` = capacity of `out` in ints; *n = ints needed (written even when cap is too small, then
  * TL_ERR_WORKSPACE_TOO_SMALL is returned).
  */

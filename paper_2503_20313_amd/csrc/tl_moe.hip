@@ -93,7 +93,8 @@ constexpr int kRouteWaves = kRouteThreads / 64;
 constexpr int kLdsTiles = 2048;  // channel masks are collected in LDS up to this many tiles, else in global memory
 constexpr int kRouteAhead = 8;
 
-// n / d for 0 <= n < 2^31 as a multiplication by a 32-bit reciprocal (round-up method: m = floor(2^32 (2^l - d) / d) + 1
+// n / d for 0 <= n < 2^31 as a multiplication by a 32-bit reciprocal (the round-up method of Granlund and Montgomery,
+// "Division by Invariant Integers using Multiplication", 1994: m = floor(2^32 (2^l - d) / d) + 1
 // with l = ceil(log2 d), n / d = (mulhi(m, n) + n) >> l).
 struct FastDiv {
   unsigned mul, shift;

@@ -27,7 +27,8 @@ def shared(M, N, K, **kw):
 @pytest.mark.parametrize("mode", ["waves", "side"])
 @pytest.mark.parametrize("M,N,K,R,C", [(2, 8, 2048, 2, 1),            # one ragged tile, two parts
                                        (256, 264, 2056, 2, 2),        # two parts, the second with a K tail of 8
-                                       (130, 392, 8200, 2, 1),        # eight parts, K tail, 65 rows per rank
+                                       (130, 392, 8200, 2, 1),        # seven parts, K tail, 65 rows per rank
+                                       (130, 392, 16392, 2, 1),       # eight, the most
                                        (1024, 1152, 3144, 8, 4)])     # 72 tiles: three parts of a K that three does not divide
 def test_shared_tiles(M, N, K, R, C, mode):
     w = wl.ag_gemm_inputs(M, N, K, R, config_id=161)
@@ -39,8 +40,8 @@ def test_shared_tiles(M, N, K, R, C, mode):
     assert flags.tolist() == [3 * info["expected_per_channel"]] * (R * C)
 
 
-def test_shared_tiles_do_not_depend_on_who_comes_last():
-    """Integer-valued inputs: every partial sum is exact in fp32, so the result must match bit for bit, call after call."""
+def test_shared_tiles_exact_small_integers():
+    """Integer-valued inputs: every partial sum is exact in fp32, so the result must match bit for bit."""
     from oracle.bf16 import round_to_bf16
     rng = np.random.default_rng(6)
     R, M, N, K = 2, 256, 256, 4096
@@ -50,6 +51,32 @@ def test_shared_tiles_do_not_depend_on_who_comes_last():
     _, _, c, _, _ = run_ag_gemm(w, 1, 1, tl.TL_COMM_WAVES)
     _, _, c_ref = ops.ag_gemm(shards, w["b"])
     assert np.array_equal(c, c_ref)
+
+
+@pytest.mark.parametrize("mode", ["waves", "none"])
+def test_shared_tiles_do_not_depend_on_who_comes_last(mode):
+    """Seven parts of N(0, 1) sums, whose fp32 rounding shows the order they are added in: the same call again and again gives
+    the same bits, whichever workgroup comes last."""
+    M, N, K, R = 512, 512, 8192, 2
+    w = wl.ag_gemm_inputs(M, N, K, R, config_id=166)
+    ctx = make_ctx(world_size=R, rank=1, comm_mode=MODES[mode])
+    ws_bytes, n_flags = tl.tl_query_workspace(ctx, tl.TL_OP_AG_GEMM, [M, N, K])
+    assert ws_bytes >= 256 + 16 * 7 * 128 * 128 * 4
+    shards = [up(s) for s in w["a_shards"]]
+    gathered, b = up(np.concatenate(w["a_shards"])), up(w["b"])
+    flags, wsp = torch.zeros(n_flags, dtype=torch.int32, device=dev()), torch.zeros(ws_bytes // 4, dtype=torch.int32, device=dev())
+    first = None
+    for epoch in range(1, 31):
+        c = poison((M, N))
+        torch.cuda.synchronize()
+        tl.tl_ag_gemm(ctx, shards, gathered, b, c, M, N, K, flags, epoch, wsp, ws_bytes)
+        torch.cuda.synchronize()
+        tl.tl_check_status(ctx, wsp)
+        if first is None:
+            first = c
+            assert_close_bf16(down(c), ops.ag_gemm(w["a_shards"], w["b"])[2], "seven parts")
+        assert torch.equal(c, first), epoch
+    tl.tl_ctx_destroy(ctx)
 
 
 @pytest.mark.parametrize("act", ["silu", "gelu"])
