@@ -440,6 +440,39 @@ static int choose_splits(long tiles, int K, int cus, double* us) {
   return best;
 }
 
+// Reduce tile where none is given: the GEMM tile, with the largest divisor of the segment up to its rows.  Where a segment
+// is not whole small tiles that divisor may be anything from 1 on; if the large tile's is not as thin (251 rows a segment:
+// 251, against 1), the reduce tile is the large GEMM tile's under either.  251 single rows of 128 columns took (us, and with
+// the large tile) [2008,608] x [608,1536] at 8 ranks 83 / 63, as a ring 318 / 60, inside the GEMM launch (K = 3584) 1392 / 102.
+struct ReduceTile { int rows, cols; };
+constexpr int kThinRows = 32;
+static ReduceTile default_reduce_tile(int variant, int segment, int N) {
+  auto rows_up_to = [&](int most) {
+    int rows = most <= segment ? most : segment;
+    while (rows > 1 && segment % rows) rows--;
+    return rows;
+  };
+  int v = variant, rows = rows_up_to(kTileM[v]);
+  if (v == TILE_128x128 && rows < segment && rows != kTileM[v] && rows_up_to(kTileM[TILE_256x256]) >= kThinRows) {
+    v = TILE_256x256;
+    rows = rows_up_to(kTileM[v]);
+  }
+  return {rows, N % kTileN[v] == 0 ? kTileN[v] : N};
+}
+
+// What thin reduce tiles (a segment of a prime number of rows, say) add to a call: each costs a wait and a notification,
+// whatever its size -- about 3.2 us of a workgroup of the side kernel, which handles those of the own segment or, where it
+// moves every segment, all; 1 us of one inside the GEMM launch, which looks at all.  Half as wide under the small GEMM tile,
+// there are twice as many: [3544,608] x [608,1536] at 8 ranks 125 us, 86 with the large one.
+static double thin_reduce_us(const tl_config& c, int variant, int M, int N, int n_comm) {
+  const int segment = M / c.world_size;
+  const ReduceTile t = default_reduce_tile(variant, segment, N);
+  if (t.rows >= kThinRows || t.rows == segment || c.comm_tile_m || c.comm_mode == TL_COMM_NONE) return 0;
+  const bool waves = c.comm_mode == TL_COMM_WAVES;
+  const double tiles = (double)((waves || !c.rs_direct_push) ? M : segment) / t.rows * (N / t.cols);
+  return (waves ? 1.0 : 3.2) * tiles / n_comm;
+}
+
 // Time of the reduce side inside the GEMM launch (TL_COMM_WAVES): its workgroups have as many threads as the tile, and
 // what each moves is bound by the bytes those keep in flight: with 256 threads about 8.5 KB a microsecond where it sums
 // the own segment over all ranks (7 at two ranks, 10 at eight), 22 where it adds two sources at a time and copies (the
@@ -494,6 +527,10 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
     if (waves_rs) {
       us_small += reduce_us(c, M, N, n_comm < cus ? n_comm : cus, false);
       us_large += reduce_us(c, M, N, n_comm < cus ? n_comm : cus, true);
+    }
+    if (op == TL_OP_GEMM_RS) {
+      us_small += thin_reduce_us(c, TILE_128x128, M, N, n_comm < cus ? n_comm : cus);
+      us_large += thin_reduce_us(c, TILE_256x256, M, N, n_comm < cus ? n_comm : cus);
     }
     // A reduce side that moves every segment slows the small tile down from its second round on, in either binding: ring,
     // side kernel, 128x128 against 256x256 (us): 256 tiles, K = 1792 60 / 69; 288 76 / 66; 512 86 / 73; 1152 202 / 137.
@@ -603,12 +640,9 @@ int resolve_dense(const tl_ctx* ctx, int op, int M, int N, int K, Resolved* r, b
       if (c.tile_order == TL_ORDER_ARRIVAL && r->nbm % R == 0 && R > 1) r->arrival_bpr = r->nbm / R;
     }
   } else {
-    int Tm_r = c.comm_tile_m;
-    if (Tm_r == 0) {   // the GEMM tile's rows, or the largest divisor of M/R below that
-      Tm_r = r->tile_m <= r->rows_per_rank ? r->tile_m : r->rows_per_rank;
-      while (Tm_r > 1 && r->rows_per_rank % Tm_r) Tm_r--;
-    }
-    int Tn_r = c.comm_tile_n ? c.comm_tile_n : (N % r->tile_n == 0 ? r->tile_n : N);
+    const ReduceTile rt = default_reduce_tile(v, r->rows_per_rank, N);
+    const int Tm_r = c.comm_tile_m ? c.comm_tile_m : rt.rows;
+    const int Tn_r = c.comm_tile_n ? c.comm_tile_n : (c.comm_tile_m ? (N % r->tile_n == 0 ? r->tile_n : N) : rt.cols);
     if (Tm_r <= 0 || r->rows_per_rank % Tm_r) return fail(TL_ERR_UNSUPPORTED_SHAPE, "reduce row tile %d must divide M/R=%d", Tm_r, r->rows_per_rank);
     if (Tn_r <= 0 || N % Tn_r || Tn_r % 8) return fail(TL_ERR_UNSUPPORTED_SHAPE, "reduce column tile %d must divide N=%d and be a multiple of 8", Tn_r, N);
     r->Tm_p = Tm_r;

@@ -117,6 +117,17 @@ def test_more_reduce_workgroups_than_compute_units(wgs, direct):
     check(w, ha, partial, push, out, f"{wgs} reduce workgroups, direct={direct}", direct=bool(direct))
 
 
+@pytest.mark.parametrize("direct", [0, 1, 2])
+@pytest.mark.parametrize("mode", ["waves", "side"])
+@pytest.mark.parametrize("segment,N", [(251, 512), (146, 264), (443, 256)])
+def test_reduce_tile_of_ragged_segments(segment, N, mode, direct):
+    """Segments of a prime number of rows and the like under the small tile: reduce tiles that several GEMM tiles share in
+    both directions, the last column tile ragged, or of one row each."""
+    w = wl.gemm_rs_inputs(4 * segment, N, 200, 4, 1, config_id=29)
+    ha, partial, push, out, flags, info = run_gemm_rs(w, MODES[mode], epochs=2, tile_m=128, tile_n=128, rs_direct_push=direct)
+    check(w, ha, partial, push, out, f"segments of {segment} rows, {mode}, direct={direct}", direct=bool(direct))
+
+
 def test_default_reduce_tile_divides_the_segment():
     """M/R = 224 rows per segment, no reduce tile given: the library picks a row count that divides the segment (112
     under 128-row GEMM tiles) instead of refusing the shape."""

@@ -99,6 +99,14 @@ def test_ragged_tiles_and_natural_order():
     check(w, ha, partial, push, out, "ring ragged side, natural order")
 
 
+@pytest.mark.parametrize("mode", ["waves", "side"])
+@pytest.mark.parametrize("segment,N", [(251, 512), (443, 256)])
+def test_reduce_tile_of_ragged_segments(segment, N, mode):
+    """Segments of a prime number of rows under the small tile: reduce tiles that several GEMM tiles share, or of one row."""
+    w = wl.gemm_ring_rs_inputs(4 * segment, N, 200, 4, 1, config_id=58)
+    check(w, *run_ring(w, MODES[mode], epochs=2, tile_m=128, tile_n=128)[:4], f"ring, segments of {segment} rows, {mode}")
+
+
 def test_single_rank_and_direct_push_ignored():
     w = wl.gemm_ring_rs_inputs(256, 256, 128, 1, 0, config_id=83)
     ha, partial, push, out, _, _ = run_ring(w, tl.TL_COMM_WAVES, comm_workgroups=2)

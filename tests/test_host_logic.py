@@ -250,3 +250,24 @@ def test_tile_shape_counts_what_else_the_call_does(op, mode, dims, kw, tile):
     ctx = host_ctx(world_size=8, comm_mode=mode, **kw)
     assert tl.tl_resolve(ctx, op, dims)["tile_m"] == tile
     tl.tl_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("segment,N,tile,reduce_tile", [
+    (256, 1536, 128, (128, 128)), (64, 1536, 128, (64, 128)), (36, 1536, 128, (36, 128)),        # whole tiles, or less than one
+    (251, 1536, 128, (251, 256)), (192, 512, 128, (192, 256)), (146, 520, 128, (146, 520)),      # the large tile's under the small one
+    (443, 1536, 128, (1, 128)), (974, 1536, 128, (2, 128)), (443, 1536, 256, (1, 256)),          # thin under either
+    (251, 1536, 256, (251, 256)), (320, 1536, 256, (160, 256))])
+def test_reduce_tile_of_ragged_segments(segment, N, tile, reduce_tile):
+    ctx = host_ctx(world_size=8, comm_mode=tl.TL_COMM_SIDE_KERNEL, tile_m=tile, tile_n=tile)
+    info = tl.tl_resolve(ctx, tl.TL_OP_GEMM_RS, [8 * segment, N, 608])
+    assert (info["comm_tile_m"], info["comm_tile_n"]) == reduce_tile
+    tl.tl_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("mode", [tl.TL_COMM_WAVES, tl.TL_COMM_SIDE_KERNEL])
+@pytest.mark.parametrize("direct", [0, 1])
+def test_thin_reduce_tiles_take_the_large_tile(mode, direct):
+    """443 rows a segment, a prime: reduce tiles of one row, twice as many under the small tile (125 / 86 us side kernel)."""
+    ctx = host_ctx(world_size=8, comm_mode=mode, rs_direct_push=direct)
+    assert tl.tl_resolve(ctx, tl.TL_OP_GEMM_RS, [8 * 443, 1536, 608])["tile_m"] == 256
+    tl.tl_ctx_destroy(ctx)
