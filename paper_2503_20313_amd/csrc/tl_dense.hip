@@ -36,7 +36,7 @@ struct GemmRsParams {
   int K;
   Sched sched;
   int n_comm, do_compute, do_notify;
-  int comm_at;          // where the reduce workgroups stand in the grid: 0, or behind the GEMM's
+  int G;                // GEMM workgroups (read where the reduce workgroups stand behind them)
 };
 
 // consumer_tile_wait inside the K loop, for AllGather channels that arrive in chunks along K: K step ks opens chunk
@@ -168,18 +168,21 @@ struct TileNotify {
   }
 };
 
-template <class Cfg>
+// BEHIND: the reduce workgroups stand behind the GEMM's in the grid (reduce_behind_gemm) and are counted as if in front.  A
+// kernel of its own: with the place as a parameter the usual form was 1-3 % slower (the ring at [8192,1792] x [1792,4096],
+// 8 ranks, in the GEMM launch 372 -> 376 us, [3544,576] x [576,768] 1443 -> 1514).
+template <class Cfg, bool BEHIND = false>
 __global__ void __launch_bounds__(Cfg::NTHREADS) gemm_rs_kernel(const GemmRsParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x;
-  const int comm_wg = (int)blockIdx.x - p.comm_at;
-  if (comm_wg >= 0 && comm_wg < p.n_comm) {
-    rs_consumer(p.rs, comm_wg, p.n_comm, tid, Cfg::NTHREADS);
+  const int wg = BEHIND ? ((int)blockIdx.x < p.G ? blockIdx.x + p.n_comm : blockIdx.x - p.G) : blockIdx.x;
+  if (wg < p.n_comm) {
+    rs_consumer(p.rs, wg, p.n_comm, tid, Cfg::NTHREADS);
     return;
   }
   if (!p.do_compute) return;
   __builtin_amdgcn_s_setprio(TL_COMPUTE_WAVE_PRIO);  // matrix waves go first when they share a SIMD with communication waves
-  const int w = p.comm_at ? blockIdx.x : blockIdx.x - p.n_comm;
+  const int w = wg - p.n_comm;
   const RsSide& rs = p.rs;
   const ClockSample cs0 = clock_sample_begin(w);
   // the 224-wide tile has no register left for the state a deferred notification carries from tile to tile
@@ -686,11 +689,11 @@ static int launch_ag_gemm(int variant, const AgGemmParams& p, int grid, hipStrea
   }
 }
 
-static int launch_gemm_rs(int variant, const GemmRsParams& p, int grid, hipStream_t s) {
+static int launch_gemm_rs(int variant, const GemmRsParams& p, int grid, hipStream_t s, bool behind = false) {
   switch (variant) {
-    case TILE_256x256: return launch_fused<Cfg256x256>(gemm_rs_kernel<Cfg256x256>, p, grid, s);
-    case TILE_256x224: return launch_fused<Cfg256x224>(gemm_rs_kernel<Cfg256x224>, p, grid, s);
-    default: return launch_fused<Cfg128x128>(gemm_rs_kernel<Cfg128x128>, p, grid, s);
+    case TILE_256x256: return launch_fused<Cfg256x256>(behind ? gemm_rs_kernel<Cfg256x256, true> : gemm_rs_kernel<Cfg256x256>, p, grid, s);
+    case TILE_256x224: return launch_fused<Cfg256x224>(behind ? gemm_rs_kernel<Cfg256x224, true> : gemm_rs_kernel<Cfg256x224>, p, grid, s);
+    default: return launch_fused<Cfg128x128>(behind ? gemm_rs_kernel<Cfg128x128, true> : gemm_rs_kernel<Cfg128x128>, p, grid, s);
   }
 }
 
@@ -1070,8 +1073,8 @@ static int gemm_rs_impl(const char* name, bool ring, tl_ctx* ctx, const void* a,
     case TL_COMM_WAVES:
       if (int e = peers_arrive(alone ? cs : ms)) return e;
       p.n_comm = r.n_comm; p.do_notify = alone ? 0 : 1; p.rs.do_wait = alone ? 0 : 1;
-      p.comm_at = !alone && reduce_behind_gemm(r.n_comm, ctx->num_cus) ? r.G : 0;
-      return launch_gemm_rs(r.variant, p, alone ? r.n_comm : r.G + r.n_comm, cs);
+      p.G = r.G;
+      return launch_gemm_rs(r.variant, p, alone ? r.n_comm : r.G + r.n_comm, cs, !alone && reduce_behind_gemm(r.n_comm, ctx->num_cus));
     case TL_COMM_EXTERNAL:
       return fail(TL_ERR_INVALID_ARG, "%s: TL_COMM_EXTERNAL is not defined for this operator", name);
     case TL_COMM_COPY_ENGINE:
